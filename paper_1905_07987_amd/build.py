@@ -53,7 +53,7 @@ def generate_tables() -> str:
 # the names their #include directives use.
 RTC_HEADERS = [("kernels.hpp", "csrc/kernels.hpp"), ("adg_internal.hpp", "csrc/adg_internal.hpp"),
                ("pde.hpp", "csrc/pde.hpp"), ("tables_gen.hpp", "csrc/tables_gen.hpp"),
-               ("predict64.hpp", "csrc/predict64.hpp"),
+               ("predict64.hpp", "csrc/predict64.hpp"), ("predict_line.hpp", "csrc/predict_line.hpp"),
                ("basis.hpp", "csrc/basis.hpp"), ("adjoint.hpp", "csrc/adjoint.hpp"),
                ("user_pde.hpp", "csrc/user_pde.hpp"), ("../../include/adg.h", "../include/adg.h")]
 

@@ -2203,6 +2203,7 @@ count_kernel(unsigned long long* __restrict__ slots, int32_t* __restrict__ count
 }  // namespace adg
 
 #include "predict64.hpp"
+#include "predict_line.hpp"
 #include "adjoint.hpp"
 
 #if !defined(__HIPCC_RTC__)
@@ -2258,6 +2259,28 @@ struct Launch {
   }
   static int blocks_b(const KArgs& a) { return (int)((a.ncells + GB::CPB - 1) / GB::CPB); }
 
+  // The line kernel, where a lane's nodes fit its registers.  Its matrix
+  // instructions (n = 4) spread a non-finite value over a plane of the cell's
+  // nodes at once, the LDS forms along three lines per pass; from three
+  // passes on, and after the four stages of the CERK guess, both have it
+  // everywhere in that cell, so fewer passes stay on the one-thread-per-node
+  // kernel.
+  static constexpr bool kLine = GeoLine<PDE, N>::fits && !PDE::kLinear, kLineAlways = kLine && !GeoLine<PDE, N>::MF;
+  static bool use_line(const KArgs& a) {
+    return kLineAlways || (kLine && (a.guess == ADG_GUESS_CERK || a.picard_iters >= 3));
+  }
+  static void launch_line(KArgs& a, const double* Q, const double* params, const double* clock, double* Qout,
+                          double* traces, hipStream_t st) {
+    if constexpr (kLine) {
+      using GA = GeoLine<PDE, N>;
+      a.nblocks = blocks_a<GA>(a);
+      const auto k = a.nsrc > 0 ? predict_kernel_line<PDE, N, kLineSources>
+                                : (a.guess == ADG_GUESS_CERK ? predict_kernel_line<PDE, N, kLineCerk>
+                                                             : predict_kernel_line<PDE, N, kLinePlain>);
+      hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(GA::BLOCK), 0, st, a, Q, params, clock, Qout, traces);
+    }
+  }
+
   static hipError_t predict(const KArgs& a0, int precision, const double* Q, const double* params,
                             const double* clock, double* Qout, double* traces, int flux_traces,
                             hipStream_t st) {
@@ -2293,6 +2316,9 @@ struct Launch {
         hipLaunchKernelGGL((predict_kernel_node<PDE, N, float, true>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
                            st, a, Q, params, clock, Qout, traces);
       }
+    } else if (use_line(a)) {
+      launch_line(a, Q, params, clock, Qout, traces, st);
+    } else if constexpr (kLineAlways) {
     } else if constexpr (UseN64<PDE, N>::value) {
       using GA = GeoN64<PDE, N>;
       a.nblocks = blocks_a<GA>(a);

@@ -66,7 +66,11 @@ struct Euler {
       const R ud = Q[1 + d] * irho;
       F[d][0] = Q[1 + d];
 #pragma unroll
-      for (int a = 0; a < DIM; ++a) F[d][1 + a] = ud * Q[1 + a];
+      for (int a = 0; a < DIM; ++a) {
+        // FP64: the symmetric products once (the FP32 form keeps its rounding)
+        if (sizeof(R) == 8 && a < d) F[d][1 + a] = F[a][1 + d];
+        else F[d][1 + a] = ud * Q[1 + a];
+      }
       F[d][1 + d] += p;
       F[d][DIM + 1] = ud * Ep;
     }
