@@ -13,8 +13,8 @@
 // Spatial derivatives go through LDS: the node threads write the fluxes (and
 // the quantities the non-conservative product differentiates) of two time
 // slices as one 16-byte element per (channel, node) into line-major rows
-// (one slice in 8-byte elements for 3-D cells of 4^3 nodes, whose waves are
-// bounded by LDS), one thread per (direction, channel, line) differentiates
+// (one slice in 8-byte elements for 3-D cells of 4^3 and 5^3 nodes, whose
+// waves are bounded by LDS), one thread per (direction, channel, line) differentiates
 // its line in place, and the node threads read their derivatives back.
 #pragma once
 
@@ -53,8 +53,10 @@ struct GeoN64 {
   // 4^3 nodes is one wave, which needs few registers; there LDS bounds the
   // waves per CU, so the rounds take one slice (8-byte elements) and the
   // final phase one direction at a time: half and a third of the LDS, twice
-  // the waves per CU.
-  static constexpr bool PAIR = !(DIM == 3 && n == 4 && !PDE::kHasNcp && NV <= 5);
+  // the waves per CU.  The same holds for two-wave cells of 5^3 nodes (43 KB
+  // per block in pairs, 1.5 waves per SIMD): 37 x 26 x 19 cells 0.79 -> 0.63
+  // ms per launch.
+  static constexpr bool PAIR = !(DIM == 3 && (n == 4 || n == 5) && !PDE::kHasNcp && NV <= 5);
   static constexpr bool FINDIR = !PAIR;
   // Picard rounds' rows: RS elements between rows, EI between a line's points
   static constexpr bool GPM = PM && PAIR;
