@@ -2206,6 +2206,41 @@ count_kernel(unsigned long long* __restrict__ slots, int32_t* __restrict__ count
 #include "predict_line.hpp"
 #include "adjoint.hpp"
 
+namespace adg {
+
+// Which FP64 predictor takes a PDE that is not linear in Q (also used for
+// run-time PDEs):
+//  line  one lane per line of nodes (predict_kernel_line): 3-D N <= 3; 2-D
+//        N = 2, 3 from kLineCells2 cells on (fewer, longer waves: N = 3,
+//        100^2 cells 21.3 us against 20.5, 150^2 32.5 against 38.3, 300^2
+//        90 against 118).  Its matrix instructions (3-D N = 3) spread a
+//        non-finite value over a plane of the cell's nodes at once, the LDS
+//        forms along three lines per pass; from three passes on, and after
+//        the four stages of the CERK guess, both have it everywhere in that
+//        cell, so fewer passes stay on the one-thread-per-node kernel.
+//  n64   one thread per node (predict_kernel_n64) where a cell fits one block
+//        of at most four waves; 2-D cells of 5^2 .. 7^2 nodes packed into
+//        blocks of several waves from kPackCells cells on (below, all waves
+//        are on the chip at once and what counts is the time of one: N = 4,
+//        64^2 cells packed 28.5 us, one wave 24.7; 80^2 35.4 against 41.0;
+//        N = 6, 64^2 89.6 against 80.8, 80^2 107 against 132).
+//  pair  a lane pair per node (predict_kernel_pair): everything else.
+template <class PDE, int N>
+struct Choose64 {
+  static constexpr long long kLineCells2 = 15000, kPackCells = 5000;
+  static constexpr bool kLine = GeoLine<PDE, N>::fits && !PDE::kLinear;
+  static constexpr bool kLineAlways = kLine && PDE::DIM == 3 && !GeoLine<PDE, N>::MF;
+  static constexpr bool kN64 = GeoN64<PDE, N>::fits;
+  static constexpr bool kCanPack = kN64 && GeoN64<PDE, N>::CAN_PACK;
+  __host__ __device__ static constexpr bool line(long long ncells, int guess, int iters) {
+    if (PDE::DIM == 2) return kLine && ncells >= kLineCells2;
+    return kLineAlways || (kLine && (guess == ADG_GUESS_CERK || iters >= 3));
+  }
+  __host__ __device__ static constexpr bool pack(long long ncells) { return kCanPack && ncells >= kPackCells; }
+};
+
+}  // namespace adg
+
 #if !defined(__HIPCC_RTC__)
 namespace adg {
 
@@ -2236,42 +2271,21 @@ __global__ void __launch_bounds__(64) bc_flux_kernel(const KArgs a, double* __re
     for (int k = 0; k < F; ++k) tr[((f * 2 + 1) * NV + v) * F + k] = PDE::flux_nonzero(d, v) ? Fx[d][v] : 0.0;
 }
 
-// The FP64 predictor of PDEs that are not linear in Q: one thread per node
-// (predict_kernel_n64) where a cell fits one block of at most four waves,
-// else the lane-pair kernel.
-template <class PDE, int N>
-struct UseN64 {
-#if defined(ADG_PAIR_PREDICTOR)
-  static constexpr bool value = false;
-#else
-  static constexpr bool value = GeoN64<PDE, N>::fits;
-#endif
-};
-
 template <class PDE, int N>
 struct Launch {
   using G = Geo<PDE, N>;
   using GB = GeoB<PDE, N>;
-  using GP = std::conditional_t<UseN64<PDE, N>::value, GeoN64<PDE, N>, GeoA2<PDE, N, double>>;
+  using Ch = Choose64<PDE, N>;
+  using GP = std::conditional_t<Ch::kN64, GeoN64<PDE, N>, GeoA2<PDE, N, double>>;
   template <class GA>
   static int blocks_a(const KArgs& a) {
     return (int)((a.ncells + GA::CPB - 1) / GA::CPB);
   }
   static int blocks_b(const KArgs& a) { return (int)((a.ncells + GB::CPB - 1) / GB::CPB); }
 
-  // The line kernel, where a lane's nodes fit its registers.  Its matrix
-  // instructions (n = 4) spread a non-finite value over a plane of the cell's
-  // nodes at once, the LDS forms along three lines per pass; from three
-  // passes on, and after the four stages of the CERK guess, both have it
-  // everywhere in that cell, so fewer passes stay on the one-thread-per-node
-  // kernel.
-  static constexpr bool kLine = GeoLine<PDE, N>::fits && !PDE::kLinear, kLineAlways = kLine && !GeoLine<PDE, N>::MF;
-  static bool use_line(const KArgs& a) {
-    return kLineAlways || (kLine && (a.guess == ADG_GUESS_CERK || a.picard_iters >= 3));
-  }
   static void launch_line(KArgs& a, const double* Q, const double* params, const double* clock, double* Qout,
                           double* traces, hipStream_t st) {
-    if constexpr (kLine) {
+    if constexpr (Ch::kLine) {
       using GA = GeoLine<PDE, N>;
       a.nblocks = blocks_a<GA>(a);
       const auto k = a.nsrc > 0 ? predict_kernel_line<PDE, N, kLineSources>
@@ -2279,6 +2293,15 @@ struct Launch {
                                                              : predict_kernel_line<PDE, N, kLinePlain>);
       hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(GA::BLOCK), 0, st, a, Q, params, clock, Qout, traces);
     }
+  }
+
+  template <bool PACK>
+  static void launch_n64(KArgs& a, const double* Q, const double* params, const double* clock, double* Qout,
+                         double* traces, hipStream_t st) {
+    using GA = GeoN64<PDE, N, PACK>;
+    a.nblocks = blocks_a<GA>(a);
+    hipLaunchKernelGGL((predict_kernel_n64<PDE, N, PACK>), dim3(a.nblocks), dim3(GA::BLOCK), 0, st, a, Q, params,
+                       clock, Qout, traces);
   }
 
   static hipError_t predict(const KArgs& a0, int precision, const double* Q, const double* params,
@@ -2316,14 +2339,15 @@ struct Launch {
         hipLaunchKernelGGL((predict_kernel_node<PDE, N, float, true>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
                            st, a, Q, params, clock, Qout, traces);
       }
-    } else if (use_line(a)) {
+    } else if (Ch::line(a.ncells, a.guess, a.picard_iters)) {
       launch_line(a, Q, params, clock, Qout, traces, st);
-    } else if constexpr (kLineAlways) {
-    } else if constexpr (UseN64<PDE, N>::value) {
-      using GA = GeoN64<PDE, N>;
-      a.nblocks = blocks_a<GA>(a);
-      hipLaunchKernelGGL((predict_kernel_n64<PDE, N>), dim3(a.nblocks), dim3(GA::BLOCK), 0, st, a, Q,
-                         params, clock, Qout, traces);
+    } else if constexpr (Ch::kLineAlways) {
+      return hipErrorNotSupported;  // not reached
+    } else if constexpr (Ch::kN64) {
+      if (Ch::pack(a.ncells))
+        launch_n64<Ch::kCanPack>(a, Q, params, clock, Qout, traces, st);
+      else
+        launch_n64<false>(a, Q, params, clock, Qout, traces, st);
     } else {
       using GA = GeoA2<PDE, N, double>;
       a.nblocks = blocks_a<GA>(a);

@@ -24,13 +24,19 @@ namespace adg {
 #define N64_SINGLE_WAVES 4
 #endif
 
-template <class PDE, int N>
+// PACK: 2-D cells of 5^2, 6^2 and 7^2 nodes share blocks of two or four
+// waves (see CPB).
+template <class PDE, int N, bool PACK = false>
 struct GeoN64 {
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
   static constexpr int n = G::n, S = G::S, F = G::F, DIM = G::DIM, NV = G::NV;
-  // Cells of fewer than 64 nodes share a wave.
-  static constexpr int CPB = S >= 64 ? 1 : 64 / S;
+  // Cells of fewer than 64 nodes share a wave.  PACK: of 2-D cells of 5^2,
+  // 6^2 and 7^2 nodes, which leave 14, 28 and 15 lanes of a wave idle that
+  // way, five or seven share a block of two or four waves (125 of 128, 252
+  // and 245 of 256 lanes).
+  static constexpr int CPB = PACK ? (n == 6 ? 7 : 5) : (S >= 64 ? 1 : 64 / S);
+  static constexpr bool CAN_PACK = DIM == 2 && n >= 5 && n <= 7 && C::NCH <= 8;
   static constexpr int LANES = CPB * S;
   static constexpr int BLOCK = (LANES + 63) / 64 * 64;
   // LDS rows: line-major with the odd line stride of Geo in general (a
@@ -45,9 +51,17 @@ struct GeoN64 {
   // point m at F r + l + EI m, EI = F times the rows, so that consecutive
   // line tasks touch consecutive units, also across row boundaries.
   static constexpr bool PM = n == 6 && DIM == 3;
-  static constexpr int LS = PM ? 1 : (n == 6 ? 6 : G::LS);  // elements between lines
+  // 2-D rows and 3-D n = 5: line stride and padding of a row and of a cell
+  // (elements) from a search with the bank rule over the node threads' and
+  // line tasks' access groups (bank cycles of both, odd strides -> these:
+  // 2-D n = 7 374 -> 284 per round, ideal 251; n = 6 460 -> 374, ideal 254;
+  // 3-D n = 5 180 -> 160, ideal 119)
+  static constexpr bool TIGHT = (DIM == 2 && n < 8) || (DIM == 3 && n == 5);
+  static constexpr int LS = PM ? 1 : (TIGHT ? (n == 6 ? 7 : n) : G::LS);  // elements between lines
+  static constexpr int ROW_PAD = DIM == 2 && n == 4 ? 1 : 0;
+  static constexpr int CELL_PAD = DIM == 2 ? (n == 2 ? 4 : (n == 7 ? 9 : (n == 3 || n == 5 ? 1 : 0))) : 0;
   static constexpr int ES = PM ? F : 1;                      // elements between a line's points
-  static constexpr int SP = PM ? n * F : F * LS;
+  static constexpr int SP = (PM ? n * F : F * LS) + ROW_PAD;
   __host__ __device__ static constexpr int slot(int line, int pos) { return line * LS + pos * ES; }
   // PAIR: two time slices per LDS round in 16-byte elements.  A 3-D cell of
   // 4^3 nodes is one wave, which needs few registers; there LDS bounds the
@@ -66,7 +80,8 @@ struct GeoN64 {
   __host__ __device__ static constexpr int islot(int line, int pos) { return GPM ? line + pos * EI : slot(line, pos); }
   static constexpr int ITER_ELEMS = GPM ? 2 * n * EI : (PAIR ? 2 : 1) * C::NCH * SP;
   static constexpr int FIN_ELEMS = (FINDIR ? 1 : DIM) * (NV + C::NFLUX) * SP;
-  static constexpr int CELL_ELEMS = cmax(ITER_ELEMS, FIN_ELEMS);
+  static constexpr int CELL_ELEMS =
+      cmax(ITER_ELEMS, FIN_ELEMS + (FINDIR && CPB == 1 ? NV * BLOCK : 0)) + (PAIR ? 2 : 1) * CELL_PAD;
   static constexpr int ELEMS = CPB * CELL_ELEMS;
   // The Ricker amplitudes of the point sources (n + 3 time entries per
   // source) live in the slots past the n points of each line (LS > n), which
@@ -112,13 +127,13 @@ struct HasFluxDir : std::false_type {};
 template <class PDE>
 struct HasFluxDir<PDE, n64_void_t<decltype(&PDE::template flux_dir<double>)>> : std::true_type {};
 
-template <class PDE, int N>
-__global__ void __launch_bounds__((GeoN64<PDE, N>::BLOCK), (GeoN64<PDE, N>::MIN_WAVES))
+template <class PDE, int N, bool PACK>
+__global__ void __launch_bounds__((GeoN64<PDE, N, PACK>::BLOCK), (GeoN64<PDE, N, PACK>::MIN_WAVES))
 predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ params,
                    const double* __restrict__ clock, double* Qout, double* __restrict__ traces) {
   // Q and Qout may be the same array (in-place step): each element is read
   // at the start and written at the end by the thread of its node.
-  using GN = GeoN64<PDE, N>;
+  using GN = GeoN64<PDE, N, PACK>;
   using C = Chan<PDE>;
   using T = CT<double, GN::n>;
   constexpr int n = GN::n, S = GN::S, F = GN::F, NV = GN::NV, NP = PDE::NP, DIM = GN::DIM;

@@ -41,7 +41,7 @@ struct GeoLine {
   // final phase takes q-bar and F-bar of one axis
   static constexpr int ROWS = cmax(XD, 2) * NV * n;
   static constexpr int NA = n + 3;           // source amplitudes per source
-  static constexpr bool fits = DIM == 3 && n <= 4 && !PDE::kHasNcp && NV <= 5;
+  static constexpr bool fits = (DIM == 3 || n >= 3) && n <= 4 && !PDE::kHasNcp && NV <= 5;
   // waves per SIMD the register allocator aims at (n n NV doubles per lane)
   static constexpr int MIN_WAVES = n * n * NV >= 64 ? 2 : (n * n * NV >= 36 ? 3 : 4);
 };

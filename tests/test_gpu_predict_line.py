@@ -1,7 +1,9 @@
-"""The one-lane-per-line FP64 predictor (3-D Euler, N <= 3) where it can go
-wrong: one cell, ragged last waves, sources on and off, one and two Picard
-passes (N = 3 takes the other kernel there), the CERK guess; and a NaN node,
-which stays in its own cell's results.
+"""The FP64 predictor's geometries where they can go wrong.  One lane per line
+(3-D Euler, N <= 3): one cell, ragged last waves, sources on and off, one and
+two Picard passes (N = 3 takes the other kernel there), the CERK guess; and a
+NaN node, which stays in its own cell's results.  2-D meshes on either side
+of the cell counts from which lines (N = 2, 3) and packed blocks (N = 4, 5, 6)
+are used.
 
 Bar: relative L2 <= 1e-12 against the oracle's step (the predictor's sums are
 reordered, each value is a few hundred FP64 operations: about 1e-14).
@@ -47,6 +49,29 @@ def test_step_against_oracle(order, cells, iters, guess, source):
     s.step(Q, None, clock, next_dt=False)
     torch.cuda.synchronize()
     assert rel_l2(Q.cpu().numpy(), Qo) <= TOL
+    s.close()
+
+
+@pytest.mark.parametrize("order,cells", [(2, [125, 119]), (2, [125, 121]), (3, [131, 117]), (4, [70, 71]), (4, [73, 71]),
+                                         (5, [71, 73]), (6, [67, 79])])
+@pytest.mark.parametrize("guess,source", [("constant", False), ("constant", True), ("cerk", False)])
+def test_step_2d_against_oracle(order, cells, guess, source):
+    print("[gpu-test] 2-D predictor", order, cells, guess, source, flush=True)
+    src = dict(x=[0.98, 0.97], weight=[0.0, 0.2, -0.1, 0.5], w=[0.0, 0.2, -0.1, 0.5], f0=2.0, t0=0.1, amp=1e-3)
+    P = O.problem(2, order, O.EULER, cells, cfl=0.4, sources=[src] if source else (),
+                  guess=O.GUESS_CERK if guess == "cerk" else 0)
+    s = adg.Solver(2, order, "euler", cells, cfl=0.4, initial_guess=guess)
+    if source:
+        s.set_point_sources([src])
+    Q0 = inputs.smooth_euler_state(O.node_coords(P), 19)
+    dt = O.stable_dt(P, Q0)[0]
+    Qo = O.step(P, Q0, None, dt, 0.05)
+    Q, clock = dev(Q0), dev([0.05, dt])
+    s.step(Q, None, clock, next_dt=False)
+    torch.cuda.synchronize()
+    assert rel_l2(Q.cpu().numpy(), Qo) <= TOL
+    last = P.ncells - 1  # the cell with the source, in the last block
+    assert rel_l2(Q[last].cpu().numpy(), Qo[last]) <= TOL
     s.close()
 
 
