@@ -162,11 +162,13 @@ int max_order_advection3();
 // PDEs compiled at run time (user.hip).
 struct UserTraits {
   int dim, nv, np, linear, has_ncp, has_source, has_boundary;
+  int predictor;  // FP64 predictor for the problem: 0 lane pair, 1 node, 2 node, packed cells, 3 line
 };
 struct UserModule;
-adg_status user_traits(const char* source, const std::string& arch, UserTraits* t, std::string* err);
+adg_status user_traits(const char* source, const std::string& arch, int order, int iters, long long ncells,
+                       UserTraits* t, std::string* err);
 adg_status user_module_create(const char* source, const std::string& arch, int order, int precision,
-                              bool linear_predictor, UserModule** out, std::string* err);
+                              bool linear_predictor, int predictor, UserModule** out, std::string* err);
 void user_module_destroy(UserModule* u);
 hipError_t user_predict(const UserModule* u, const KArgs& a, const double* Q, const double* params,
                         const double* clock, double* Qout, double* traces, int flux_traces, hipStream_t st);

@@ -277,7 +277,8 @@ adg_status create_ctx(const adg_config* cfg, const char* source, adg_ctx** out) 
     const std::string arch = prop.gcnArchName;
     std::string err;
     UserTraits t{};
-    adg_status st = user_traits(source, arch, &t, &err);
+    const int I = c.picard_iters ? c.picard_iters : c.order + 1;
+    adg_status st = user_traits(source, arch, c.order, I, C, &t, &err);
     if (st) return fail(st, err);
     if (t.dim != c.dim) return fail(ADG_ERR_INVALID_ARG, "AdgUserPDE::DIM differs from cfg->dim");
     for (int f = 0; f < 6; ++f)
@@ -285,8 +286,7 @@ adg_status create_ctx(const adg_config* cfg, const char* source, adg_ctx** out) 
         return fail(ADG_ERR_INVALID_ARG, "ADG_BC_USER needs AdgUserPDE::HAS_BOUNDARY and boundary_values");
     if (t.nv < 1 || t.np < 0 || t.nv + t.np > kMaxVar)
       return fail(ADG_ERR_INVALID_ARG, "AdgUserPDE: NV + NP must be in 1..16");
-    const int I = c.picard_iters ? c.picard_iters : c.order + 1;
-    st = user_module_create(source, arch, c.order, c.precision, t.linear && I <= kMaxLin, &um, &err);
+    st = user_module_create(source, arch, c.order, c.precision, t.linear && I <= kMaxLin, t.predictor, &um, &err);
     if (st) return fail(st, err);
     nv = t.nv;
     np = t.np;

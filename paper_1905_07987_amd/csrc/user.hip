@@ -23,6 +23,7 @@ extern const char* const kRtcHeaderTexts[];
 
 struct UserModule {
   hipModule_t mod = nullptr;
+  hipFunction_t predict_src = nullptr;  // with point sources (line predictor; null: predict takes them)
   hipFunction_t predict = nullptr, correct = nullptr, lambda = nullptr, admissible = nullptr;
   hipFunction_t finalize = nullptr, count = nullptr;
   int pred_block = 0, pred_cpb = 0, b_block = 0, b_cpb = 0;
@@ -102,20 +103,25 @@ std::string prelude(const char* source) {
 
 }  // namespace
 
-adg_status user_traits(const char* source, const std::string& arch, UserTraits* t, std::string* err) {
+adg_status user_traits(const char* source, const std::string& arch, int order, int iters, long long ncells,
+                       UserTraits* t, std::string* err) {
   const std::string src = prelude(source) +
-                          "extern \"C\" __constant__ int adg_user_traits[7] = {AdgUserPDE::DIM, "
+                          "using ChosenPredictor = adg::Choose64<adg::UserTerms<AdgUserPDE>, " + std::to_string(order) +
+                          ">;\nextern \"C\" __constant__ int adg_user_traits[8] = {AdgUserPDE::DIM, "
                           "AdgUserPDE::NV, AdgUserPDE::NP, (int)AdgUserPDE::LINEAR, "
                           "(int)AdgUserPDE::HAS_NCP, (int)AdgUserPDE::HAS_SOURCE, "
-                          "(int)adg::UserHasBoundary<AdgUserPDE>::value};\n";
+                          "(int)adg::UserHasBoundary<AdgUserPDE>::value, "
+                          "AdgUserPDE::HAS_NCP ? 0 : ChosenPredictor::line(" + std::to_string(ncells) + "LL, 0, " +
+                          std::to_string(iters) + ") ? 3 : ChosenPredictor::pack(" + std::to_string(ncells) +
+                          "LL) ? 2 : ChosenPredictor::kN64 ? 1 : 0};\n";
   Compiled c;
   adg_status st = rtc_compile(src, {}, arch, &c, err);
   if (st) return st;
   hipModule_t m = nullptr;
   hipError_t e = hipModuleLoadData(&m, c.code.data());
   if (e != hipSuccess) return hip_err(e, "hipModuleLoadData", err);
-  int v[7];
-  st = read_ints(m, "adg_user_traits", v, 7, err);
+  int v[8];
+  st = read_ints(m, "adg_user_traits", v, 8, err);
   (void)hipModuleUnload(m);
   if (st) return st;
   t->dim = v[0];
@@ -125,15 +131,16 @@ adg_status user_traits(const char* source, const std::string& arch, UserTraits* 
   t->has_ncp = v[4];
   t->has_source = v[5];
   t->has_boundary = v[6];
+  t->predictor = v[7];
   return ADG_OK;
 }
 
 adg_status user_module_create(const char* source, const std::string& arch, int order, int precision,
-                              bool linear_predictor, UserModule** out, std::string* err) {
+                              bool linear_predictor, int predictor, UserModule** out, std::string* err) {
   *out = nullptr;
   const std::string N = std::to_string(order);
   const std::string UP = "adg::UserTerms<::AdgUserPDE>";
-  std::string pred, geo;
+  std::string pred, pred_src, geo;
   if (linear_predictor) {
     const char* R = precision == ADG_MIXED_FP32 ? "float" : "double";
     pred = "adg::predict_kernel_lin<" + UP + ", " + N + ", " + R + ">";
@@ -141,6 +148,14 @@ adg_status user_module_create(const char* source, const std::string& arch, int o
   } else if (precision == ADG_MIXED_FP32) {
     pred = "adg::predict_kernel_node<" + UP + ", " + N + ", float>";
     geo = "adg::GeoA1<" + UP + ", " + N + ", float>";
+  } else if (predictor == 3) {
+    pred = "adg::predict_kernel_line<" + UP + ", " + N + ", adg::kLinePlain>";
+    pred_src = "adg::predict_kernel_line<" + UP + ", " + N + ", adg::kLineSources>";
+    geo = "adg::GeoLine<" + UP + ", " + N + ">";
+  } else if (predictor > 0) {
+    const char* pack = predictor == 2 ? "true" : "false";
+    pred = "adg::predict_kernel_n64<" + UP + ", " + N + ", " + pack + ">";
+    geo = "adg::GeoN64<" + UP + ", " + N + ", " + pack + ">";
   } else {
     pred = "adg::predict_kernel_pair<" + UP + ", " + N + ", double>";
     geo = "adg::GeoA2<" + UP + ", " + N + ", double>";
@@ -148,12 +163,13 @@ adg_status user_module_create(const char* source, const std::string& arch, int o
   const std::string gb = "adg::GeoB<" + UP + ", " + N + ">";
   const std::string src = prelude(source) + "extern \"C\" __constant__ int adg_user_geo[4] = {" + geo +
                           "::BLOCK, " + geo + "::CPB, " + gb + "::BLOCK, " + gb + "::CPB};\n";
-  const std::vector<std::string> names = {"&" + pred,
+  std::vector<std::string> names = {"&" + pred,
                                           "&adg::correct_kernel<" + UP + ", " + N + ">",
                                           "&adg::lambda_kernel<" + UP + ", " + N + ">",
                                           "&adg::admissible_kernel<" + UP + ", " + N + ">",
                                           "&adg::finalize_kernel",
                                           "&adg::count_kernel"};
+  if (!pred_src.empty()) names.push_back("&" + pred_src);
   Compiled c;
   adg_status st = rtc_compile(src, names, arch, &c, err);
   if (st) return st;
@@ -163,7 +179,8 @@ adg_status user_module_create(const char* source, const std::string& arch, int o
     delete u;
     return hip_err(e, "hipModuleLoadData", err);
   }
-  hipFunction_t* fs[] = {&u->predict, &u->correct, &u->lambda, &u->admissible, &u->finalize, &u->count};
+  hipFunction_t* fs[] = {&u->predict, &u->correct, &u->lambda, &u->admissible, &u->finalize, &u->count,
+                         &u->predict_src};
   for (size_t i = 0; i < names.size(); ++i) {
     e = hipModuleGetFunction(fs[i], u->mod, c.lowered[i].c_str());
     if (e != hipSuccess) {
@@ -203,7 +220,7 @@ hipError_t user_predict(const UserModule* u, const KArgs& a0, const double* Q, c
   a.flux_traces = flux_traces;
   a.nblocks = (int)((a.ncells + u->pred_cpb - 1) / u->pred_cpb);
   void* args[] = {&a, &Q, &params, &clock, &Qout, &traces};
-  return launch(u->predict, a.nblocks, u->pred_block, st, args);
+  return launch(u->predict_src && a.nsrc > 0 ? u->predict_src : u->predict, a.nblocks, u->pred_block, st, args);
 }
 
 hipError_t user_correct(const UserModule* u, const KArgs& a0, double* Q, const double* params, double* clock,

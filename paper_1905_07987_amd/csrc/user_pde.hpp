@@ -78,6 +78,13 @@ struct UserTerms {
   }
 
   template <class R>
+  __device__ static __forceinline__ void flux_dir(const R* Q, const R* P, const PdeConsts&, int d, R* F) {
+    R q[NV + NP];
+    gather(Q, P, q);
+    U::flux(q, d, F);
+  }
+
+  template <class R>
   __device__ static __forceinline__ void ncp(const R* Q, const R* P, const PdeConsts&, const R (*g)[NV],
                                              R* B) {
     if constexpr (U::HAS_NCP) {

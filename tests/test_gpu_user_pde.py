@@ -279,3 +279,21 @@ def test_user_boundary_values_vs_oracle():
     with pytest.raises(adg.AdgError) as ei:
         adg.Solver(3, 2, "euler", cells, bc=["user", "user", 0, 0, 0, 0])
     assert ei.value.status == -1
+
+
+@pytest.mark.parametrize("order", [2, 3])
+def test_user_euler_point_source_vs_builtin(order):
+    """The run-time PDE's predictor with a point source (its own kernel where
+    lines are used) against the built-in Euler's."""
+    cells = [3, 2, 3]
+    src = dict(x=[0.4, 0.3, 0.7], weight=[0.0, 0.1, 0.2, -0.1, 0.4], f0=2.0, t0=0.1, amp=0.02)
+    P = O.problem(3, order, O.EULER, cells)
+    Q0 = inputs.smooth_euler_state(O.node_coords(P), 83)
+    out = []
+    for kw in (dict(source=EULER3), {}):
+        s = adg.Solver(3, order, "euler", cells, **kw)
+        s.set_point_sources([src])
+        out.append(run(s, Q0, None, 2)[0])
+        s.close()
+    assert rel_l2(out[0], out[1]) <= TOL
+    assert rel_l2(out[1], Q0) > 1e-6
