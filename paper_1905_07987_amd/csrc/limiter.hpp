@@ -45,14 +45,29 @@ struct GeoLim {
   static constexpr int NS = ipow(m, DIM), NSF = ipow(m, DIM - 1);
   static constexpr int EB = m + 4, NB = ipow(EB, DIM);  // subcells of the cell and two ghost layers
   static constexpr int EC = m + 2, NC = ipow(EC, DIM);  // subcells whose face values are moved
-  static constexpr int NTAB = 3 * m * n;                // A [m][n], B [n][m], Qf [n][m]
-  static constexpr int BLOCK = 512;                     // threads of the FV kernel
+  static constexpr int NTAB = m * n;                    // A [m][n]
+  // threads of the FV kernel: its phases in one round each where that fits
+  // (3-D N = 3: 720 lines along x, 729 subcells with moved faces)
+  static constexpr int BLOCK = DIM == 2 ? 256 : (N == 3 ? 768 : (N == 2 ? 512 : 256));
   static constexpr int VPT = (NS + BLOCK - 1) / BLOCK;  // subcells per thread in the update
-  static constexpr int NOWN = DIM == 3 ? 19 : 9;        // the cell, its face and edge neighbours
-  // fv: tables, the subcell box, then either the owners' nodal values (while
-  // the box is filled) or the half-step corrections and the subface fluxes
-  static constexpr int FV_D = NTAB + NV * NB + cmax(NV * (NC + 2 * DIM * NSF), NOWN * NV * S);
-  static constexpr bool built = LimiterPDE<PDE>::value && FV_D * 8 + NC <= 120 * 1024;
+  static constexpr int PPT = (NB + BLOCK - 1) / BLOCK;  // box positions per thread
+  static constexpr int NOFF = ipow(3, DIM);             // offsets of the cell and its neighbours
+  static constexpr int NFC = ipow(m, DIM - 1) * (m + 1);  // subfaces normal to one axis
+  // LDS of the FV kernel (doubles).  REG_A: the projection along x, then the
+  // subcell box, then the fit's first stages.  REG_B: (3-D) the projection
+  // along y, then the half-step corrections and every subface's flux.
+  static constexpr int T1 = NV * ipow(3, DIM - 1) * ipow(n, DIM - 1) * EB;
+  static constexpr int T2 = DIM == 3 ? NV * 3 * n * EB * EB : 0;
+  static constexpr int FIT = NV * (NS + ipow(m, DIM - 1) * n) + 2 * DIM * NV * ipow(m, DIM - 2) * n;
+  static constexpr int REG_A = cmax(T1, cmax(NV * NB, FIT));
+  static constexpr int REG_B = cmax(T2, NV * (NC + DIM * NFC));
+  static constexpr int FV_D = NTAB + REG_A + REG_B;
+  static constexpr bool built = LimiterPDE<PDE>::value && N <= (DIM == 2 ? 7 : 3);
+  // waves per SIMD of the register budget, blocks of the FV kernel per
+  // compute unit, and its persistent grid
+  static constexpr int FV_WAVES = DIM == 3 && N >= 2 ? (N == 3 ? 3 : 2) : 3;
+  static constexpr int FV_BPC = cmax(1, cmin(FV_WAVES * 256 / BLOCK, (160 * 1024) / (FV_D * 8 + NC + 1024)));
+  static constexpr int FV_GRID = 256 * FV_BPC;
 };
 
 template <int DIM>
@@ -469,163 +484,301 @@ __device__ __forceinline__ double lim_minmod(double x, double y) {
   return 0.0;
 }
 
-// Rusanov flux along d between the states qa (low side) and qb (high side).
-template <class PDE>
-__device__ __forceinline__ void lim_rusanov(const PdeConsts& pc, int d, const double* qa, const double* qb,
-                                            double* G) {
+// PDE::admissible without its division where the sign of the pressure is
+// clear from rho E - |j|^2 / 2 (the same answer: the two differ by rounding).
+// FIN: with the test for finite values; without it the answer for values that
+// are not finite is open.
+template <class PDE, bool FIN = true>
+__device__ __forceinline__ bool lim_admissible(const double* q, const PdeConsts& pc) {
   constexpr int NV = PDE::NV, DIM = PDE::DIM;
-  double Fa[DIM][NV], Fb[DIM][NV];
-  PDE::fluxes(qa, qa, pc, Fa);
-  PDE::fluxes(qb, qb, pc, Fb);
-  const double s = fmax(PDE::max_eigen(qa, qa, pc, d), PDE::max_eigen(qb, qb, pc, d));
+  bool fin = true;
+  if constexpr (FIN) {
 #pragma unroll
-  for (int v = 0; v < NV; ++v) G[v] = 0.5 * (Fa[d][v] + Fb[d][v]) - 0.5 * s * (qb[v] - qa[v]);
+    for (int v = 0; v < NV; ++v) fin = fin && finite_val(q[v]);
+  }
+  double jj = 0.0;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) jj += q[1 + a] * q[1 + a];
+  const double rE = q[0] * q[NV - 1], t = rE - 0.5 * jj;
+  if (fin && q[0] > 0.0 && !(fabs(t) > 1e-12 * fabs(rE))) return PDE::admissible(q, q, pc);
+  return fin && q[0] > 0.0 && t > 0.0;
 }
 
-// The value of box position p extrapolated to its face (d, side) and moved
-// half a step (its average where the subcell falls back to first order).
+// Rusanov flux along the axis whose momentum is component 1, between the
+// states qa (low side) and qb (high side).
+template <class PDE>
+__device__ __forceinline__ void lim_rusanov(const PdeConsts& pc, const double* qa, const double* qb, double* G) {
+  constexpr int NV = PDE::NV, DIM = PDE::DIM;
+  double F[2][NV], s[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const double* q = h ? qb : qa;
+    const double irho = 1.0 / q[0];
+    double jj = 0.0;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) jj += q[1 + a] * q[1 + a];
+    const double p = (pc.gamma - 1.0) * (q[NV - 1] - 0.5 * jj * irho);
+    const double u = q[1] * irho;
+    F[h][0] = q[1];
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) F[h][1 + a] = a == 0 ? u * q[1] + p : u * q[1 + a];
+    F[h][NV - 1] = u * (q[NV - 1] + p);
+    s[h] = fabs(u) + sqrt(pc.gamma * p * irho);
+  }
+  const double sm = fmax(s[0], s[1]);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) G[v] = 0.5 * (F[0][v] + F[1][v]) - 0.5 * sm * (qb[v] - qa[v]);
+}
+
+// The values of box position p extrapolated to its face on side `side` of the
+// axis with box stride sd and moved half a step (its averages where the
+// subcell falls back to first order); component v at cv[v] of the box.
 template <class PDE, int N>
 __device__ __forceinline__ void lim_moved(const double* box, const double* corr, const uint8_t* okf, int p, int q,
-                                          int d, int side, double (&out)[PDE::NV]) {
+                                          int sd, int side, const int (&cv)[PDE::NV], double (&out)[PDE::NV]) {
   using GL = GeoLim<PDE, N>;
-  constexpr int NV = GL::NV, NB = GL::NB, NC = GL::NC, EB = GL::EB;
-  const int sd = d == 0 ? 1 : (d == 1 ? EB : EB * EB);
+  constexpr int NV = GL::NV, NB = GL::NB, NC = GL::NC;
   const bool ok = okf[q] != 0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const double wv = box[v * NB + p];
-    if (ok) {
-      const double slope = lim_minmod(wv - box[v * NB + p - sd], box[v * NB + p + sd] - wv);
-      out[v] = (side ? wv + 0.5 * slope : wv - 0.5 * slope) + corr[v * NC + q];
-    } else {
-      out[v] = wv;
-    }
+    const double* b = box + cv[v] * NB + p;
+    const double wv = b[0], slope = lim_minmod(wv - b[-sd], b[sd] - wv), cr = corr[cv[v] * NC + q];
+    out[v] = ok ? (side ? wv + 0.5 * slope : wv - 0.5 * slope) + cr : wv;
   }
 }
 
-// FV cells, a persistent grid over the FV list.
+// Subcell averages along one axis of a line of nodes extended by two subcells
+// on either side, from the lines of the cell (own) and of its neighbours on
+// the low and high side; a mirrored side (w[side]) repeats the own subcells
+// in reverse, times sgn[side] (-1: the normal momentum at a wall).
+template <int n>
+__device__ __forceinline__ void lim_extend(const double (&own)[n], const double (&lo)[n], const double (&hi)[n],
+                                           const bool (&w)[2], const double (&sgn)[2], double (&out)[2 * n + 3]) {
+  using LC = LimConst<n>;
+  constexpr int m = 2 * n - 1;
+  auto dot = [&](int s, const double (&x)[n]) {
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < n; ++k) acc += LC::A[s][k] * x[k];
+    return acc;
+  };
+#pragma unroll
+  for (int s = 0; s < m; ++s) out[2 + s] = dot(s, own);
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    out[g] = w[0] ? sgn[0] * out[3 - g] : dot(m - 2 + g, lo);
+    out[m + 2 + g] = w[1] ? sgn[1] * out[m + 1 - g] : dot(g, hi);
+  }
+}
+
+// FV cells, a persistent grid over the FV list.  Bound by the latency of its
+// phases, each about one round of dependent FP64 work and LDS accesses, with
+// one block of twelve waves per compute unit (3-D N = 3: 141 KB of LDS; per
+// cell 54,000 cycles, the slopes and half-step corrections 12,000, the owners'
+// data 10,000, the subface fluxes 8,700).  The box of subcell averages is a
+// tensor-product projection, an axis at a time over the cell and its
+// neighbours together (82 kFMA per cell; every position from the owner's 64
+// nodes: 426 kFMA and the LDS reads with it), each subface's flux is computed
+// once (1176 Rusanov fluxes instead of 2058), and the next cell's
+// neighbourhood is looked up beside the update.  24,000 FV cells of the 96^3
+// explosion: 3.32 -> 1.95 ms; 550 cells of 81^2, N = 5: 37 -> 16 us.
 template <class PDE, int N>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__((GeoLim<PDE, N>::BLOCK), (GeoLim<PDE, N>::FV_WAVES))
 lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __restrict__ sub_in, double* __restrict__ Q,
-              double* __restrict__ sub_out, const LimWork w) {
+              double* __restrict__ sub_out, const uint8_t* __restrict__ status, const LimWork w) {
   using GL = GeoLim<PDE, N>;
-  constexpr int DIM = GL::DIM, NV = GL::NV, S = GL::S, NS = GL::NS, NSF = GL::NSF, F = GL::F;
+  using LC = LimConst<GL::n>;
+  constexpr int DIM = GL::DIM, NV = GL::NV, S = GL::S, NS = GL::NS, NSF = GL::NSF, F = GL::F, NOFF = GL::NOFF;
   constexpr int m = GL::m, n = GL::n, EB = GL::EB, NB = GL::NB, EC = GL::EC, NC = GL::NC, BLOCK = GL::BLOCK;
+  constexpr int NL = ipow(n, DIM - 1), NOY = ipow(3, DIM - 1);
   __shared__ double lds[GL::FV_D];
   __shared__ uint8_t okf[NC];
-  __shared__ long long owner[GL::NOWN];  // owner cell of each slot, -1 beyond a non-periodic face
-  __shared__ uint8_t fvdata[GL::NOWN];   // the owner was FV at t^n: its subcell data is read
-  double* T = lds;
-  double* box = T + GL::NTAB;
-  double* corr = box + NV * NB;
-  double* fsub = corr + NV * NC;
-  double* ou = corr;  // the owners' nodal values, only while the box is filled
-  const double* A = T;
-  const double* B = T + m * n;
-  const double* Qf = T + 2 * m * n;
+  // of this cell and of the block's next: the cell at every offset in
+  // {-1,0,1}^dim (-1 beyond a non-periodic face), whether it was FV at t^n
+  // (its subcell data is read), and the faces whose neighbour is a DG cell
+  // after the step
+  __shared__ long long owner2[2][NOFF];
+  __shared__ uint8_t fvdata2[2][NOFF], dgface2[2][2 * DIM];
+  double* const T = lds;
+  double* const ra = T + GL::NTAB;
+  double* const rb = ra + GL::REG_A;
+  double* const box = ra;
+  double* const corr = rb;
+  double* const ff = rb + NV * NC;  // subface fluxes [d][t][i][v], i = 0..m along d
   const int tid = threadIdx.x;
   for (int i = tid; i < GL::NTAB; i += BLOCK) T[i] = w.tab[i];
   const double dt = clock[1];
-  double hs[3] = {1.0, 1.0, 1.0};
+  double ihs[3] = {1.0, 1.0, 1.0};  // 1 / subcell size
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) hs[d] = a.h[d] / m;
+  for (int d = 0; d < DIM; ++d) ihs[d] = m * a.inv_h[d];
   const int count = w.counters[1];
+  const int C0 = a.cells[0], C1 = a.cells[1];
+  // the neighbourhood of list entry it, by threads t0 .. t0 + NOFF - 1: one
+  // offset k in {-1,0,1}^dim with at most two nonzero entries each
+  auto neighbourhood = [&](int it, int t0) {
+    const int k = tid - t0;
+    if (it >= count || k < 0 || k >= NOFF) return;
+    const long long c = w.fv_list[it];
+    const int off[3] = {k % 3 - 1, (k / 3) % 3 - 1, DIM == 3 ? k / 9 - 1 : 0};
+    int oc[3] = {(int)(c % C0), (int)((c / C0) % C1), DIM == 3 ? (int)(c / ((long long)C0 * C1)) : 0};
+    bool exists = (off[0] != 0) + (off[1] != 0) + (off[2] != 0) <= 2;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      oc[d] += off[d];
+      if (oc[d] < 0 || oc[d] >= a.cells[d]) {
+        if (a.bc[2 * d + (off[d] > 0)] != ADG_BC_PERIODIC) exists = false;
+        oc[d] = (oc[d] + a.cells[d]) % a.cells[d];
+      }
+    }
+    const long long o = exists ? oc[0] + (long long)C0 * (oc[1] + (long long)C1 * oc[2]) : -1;
+    const uint8_t was = exists ? w.st_prev[o] : 0, is = exists ? status[o] : 3;
+    const int par = (it / (int)gridDim.x) & 1;
+    owner2[par][k] = o;
+    fvdata2[par][k] = was >= 2 ? 1 : 0;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const int one = d == 0 ? 1 : (d == 1 ? 3 : 9), mid = NOFF / 2;
+      if (k == mid - one) dgface2[par][2 * d] = is < 2;
+      if (k == mid + one) dgface2[par][2 * d + 1] = is < 2;
+    }
+  };
+  neighbourhood(blockIdx.x, 0);
   for (int it = blockIdx.x; it < count; it += gridDim.x) {
     const long long c = w.fv_list[it];
-    const int C0 = a.cells[0], C1 = a.cells[1];
     const int cc[3] = {(int)(c % C0), (int)((c / C0) % C1), DIM == 3 ? (int)(c / ((long long)C0 * C1)) : 0};
-    __syncthreads();  // the previous cell's LDS reads are done
-    // 1. the subcell box: the cell, two ghost layers across each face, one
-    //    across each edge (corners are never read).  Every position belongs
-    //    to the cell or to a face or edge neighbour (beyond a non-periodic
-    //    face it mirrors a subcell of the cell on this side, the wall
-    //    reversing the normal momentum).  The owners' nodal values are
-    //    staged in LDS first (owner slot: the offset's rank among the
-    //    offsets in {-1,0,1}^dim with at most two nonzero entries).
-    // one thread per offset k in {-1,0,1}^dim: its owner cell and whether
-    // that owner was FV at t^n
-    if (tid < ipow(3, DIM)) {
-      const int k = tid;
-      const int off[3] = {k % 3 - 1, (k / 3) % 3 - 1, DIM == 3 ? k / 9 - 1 : 0};
-      if ((off[0] != 0) + (off[1] != 0) + (off[2] != 0) <= 2) {
-        const int slot = DIM == 2 ? k
-                                  : k - ((k > 0) + (k > 2) + (k > 6) + (k > 8) + (k > 18) + (k > 20) + (k > 24));
-        int oc[3] = {cc[0], cc[1], cc[2]};
-        bool exists = true;
+    // sides beyond which the box mirrors this cell's subcells, and whether
+    // the mirror reverses the normal momentum
+    bool mir[DIM][2], wall[DIM][2];
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          oc[d] += off[d];
-          if (oc[d] < 0 || oc[d] >= a.cells[d]) {
-            if (a.bc[2 * d + (off[d] > 0)] != ADG_BC_PERIODIC) exists = false;
-            oc[d] = (oc[d] + a.cells[d]) % a.cells[d];
-          }
-        }
-        const long long o = exists ? oc[0] + (long long)C0 * (oc[1] + (long long)C1 * oc[2]) : -1;
-        owner[slot] = o;
-        fvdata[slot] = (exists && w.st_prev[o] >= 2) ? 1 : 0;
+    for (int d = 0; d < DIM; ++d)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        mir[d][g] = (g ? cc[d] == a.cells[d] - 1 : cc[d] == 0) && a.bc[2 * d + g] != ADG_BC_PERIODIC;
+        wall[d][g] = mir[d][g] && a.bc[2 * d + g] == ADG_BC_WALL;
       }
-    }
-    __syncthreads();
-    for (int i = tid; i < GL::NOWN * NV * S; i += BLOCK) {
-      const int slot = i / (NV * S), j = i - slot * NV * S;
-      if (owner[slot] >= 0 && !fvdata[slot]) ou[i] = w.Qold[owner[slot] * NV * S + j];
-    }
-    __syncthreads();
-    for (int p = tid; p < NB; p += BLOCK) {
+    const int par = (it / (int)gridDim.x) & 1;
+    const long long* const owner = owner2[par];
+    const uint8_t *const fvdata = fvdata2[par], *const dgface = dgface2[par];
+    __syncthreads();  // the neighbourhood is there, the previous cell's LDS reads are done
+    // 1. the subcell box: the cell, two ghost layers across each face, one
+    //    across each edge (corners are never read).  A position belongs to
+    //    the cell or to a face or edge neighbour (beyond a non-periodic face
+    //    it mirrors a subcell of the cell on this side).  First the
+    //    positions whose owner has FV data, kept in registers until the box
+    //    is free; then the projections of the owners' polynomials.
+    double pre[GL::PPT][NV];
+    int sgn_of[GL::PPT];  // -1: not from FV data, else bit d: component 1 + d reversed
+#pragma unroll
+    for (int j = 0; j < GL::PPT; ++j) {
+      const int p = tid + j * BLOCK < NB ? tid + j * BLOCK : 0;
       int x[3];
       lim_multi<DIM>(p, EB, x);
-      int outside = 0, far = 0, po[3] = {0, 0, 0}, ss[3] = {0, 0, 0};
-      bool flip[3] = {false, false, false};
+      int outside = 0, far = 0, k = 0, si = 0, sg = 0;
 #pragma unroll
-      for (int d = 0; d < DIM; ++d) {
+      for (int d = DIM - 1; d >= 0; --d) {
         const int r = x[d] - 2;
+        int po = 0, ss = r;
         if (r < 0 || r >= m) {
           ++outside;
-          const int side = r >= m, to = cc[d] + (side ? 1 : -1);
-          if ((to < 0 || to >= a.cells[d]) && a.bc[2 * d + side] != ADG_BC_PERIODIC) {
-            ss[d] = side ? 2 * m - 1 - r : -1 - r;
-            flip[d] = a.bc[2 * d + side] == ADG_BC_WALL;
-          } else {
-            po[d] = side ? 1 : -1;
-            ss[d] = r - po[d] * m;
-          }
-        } else {
-          ss[d] = r;
+          const int g = r >= m;
+          const bool mg = g ? mir[d][1] : mir[d][0], wg = g ? wall[d][1] : wall[d][0];
+          ss = mg ? (g ? 2 * m - 1 - r : -1 - r) : (g ? r - m : r + m);
+          po = mg ? 0 : (g ? 1 : -1);
+          if (wg) sg |= 1 << d;
         }
         if (r < -1 || r > m) ++far;
+        k = 3 * k + po + 1;
+        si = m * si + ss;
       }
-      if (outside > 2 || (outside == 2 && far > 0)) continue;
-      // slot of the offset po
-      const int kpo = (po[0] + 1) + 3 * (po[1] + 1) + (DIM == 3 ? 9 * (po[2] + 1) : 0);
-      // rank of kpo among the offsets with at most two nonzero entries: in
-      // 3-D the eight corners k = 0, 2, 6, 8, 18, 20, 24, 26 are left out
-      const int slot = DIM == 2 ? kpo
-                                : kpo - ((kpo > 0) + (kpo > 2) + (kpo > 6) + (kpo > 8) + (kpo > 18) + (kpo > 20) +
-                                         (kpo > 24));
-      const long long o = owner[slot];
-      double val[NV];
-      if (fvdata[slot]) {
-        const int si = ss[0] + m * (ss[1] + m * ss[2]);
+      const bool skip = tid + j * BLOCK >= NB || outside > 2 || (outside == 2 && far > 0) || !fvdata[k];
+      sgn_of[j] = skip ? -1 : sg;
+      const double* src = sub_in + (skip ? c : owner[k]) * (long long)(NV * NS) + si;
+      if (!skip) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) val[v] = sub_in[(o * NV + v) * NS + si];
-      } else {
-        const double* uo = ou + slot * NV * S;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) val[v] = 0.0;
-        for (int kk = 0; kk < S; ++kk) {
-          const int kx = kk % n, ky = (kk / n) % n, kz = DIM == 3 ? kk / (n * n) : 0;
-          double cf = A[ss[0] * n + kx] * A[ss[1] * n + ky];
-          if (DIM == 3) cf *= A[ss[2] * n + kz];
-#pragma unroll
-          for (int v = 0; v < NV; ++v) val[v] += cf * uo[v * S + kk];
-        }
+        for (int v = 0; v < NV; ++v) pre[j][v] = src[v * NS];
       }
-#pragma unroll
-      for (int d = 0; d < DIM; ++d)
-        if (flip[d]) val[1 + d] = -val[1 + d];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) box[v * NB + p] = val[v];
     }
+    // along x: one task per (quantity, y (and z) offset, line of nodes)
+    for (int t = tid; t < NV * NOY * NL; t += BLOCK) {
+      const int line = t % NL, ky = (t / NL) % NOY, v = t / (NL * NOY);
+      // the three owners along x: offset index ky * 3 + (0, 1, 2)
+      double x[3][n];
+#pragma unroll
+      for (int g = 0; g < 3; ++g) {
+        const long long o = owner[ky * 3 + g];
+        const double* src = w.Qold + (o >= 0 ? o : c) * (long long)(NV * S) + v * S + line * n;
+#pragma unroll
+        for (int k = 0; k < n; ++k) x[g][k] = src[k];
+      }
+      const double sgn[2] = {v == 1 && wall[0][0] ? -1.0 : 1.0, v == 1 && wall[0][1] ? -1.0 : 1.0};
+      double out[EB];
+      lim_extend<n>(x[1], x[0], x[2], mir[0], sgn, out);
+#pragma unroll
+      for (int i = 0; i < EB; ++i) ra[t * EB + i] = out[i];
+    }
+    __syncthreads();
+    // value of box position (k: offset index of its owner) of the projection,
+    // unless the owner's FV data is taken
+    if constexpr (DIM == 3) {
+      // along y: one task per (quantity, z offset, kz, x)
+      for (int t = tid; t < NV * 3 * n * EB; t += BLOCK) {
+        const int i = t % EB, kz = (t / EB) % n, oz = (t / (EB * n)) % 3, v = t / (EB * n * 3);
+        double x[3][n];
+#pragma unroll
+        for (int g = 0; g < 3; ++g)
+#pragma unroll
+          for (int k = 0; k < n; ++k) x[g][k] = ra[(((v * NOY + oz * 3 + g) * n + kz) * n + k) * EB + i];
+        const double sgn[2] = {v == 2 && wall[1][0] ? -1.0 : 1.0, v == 2 && wall[1][1] ? -1.0 : 1.0};
+        double out[EB];
+        lim_extend<n>(x[1], x[0], x[2], mir[1], sgn, out);
+        double* o = rb + ((v * 3 + oz) * n + kz) * EB * EB + i;
+#pragma unroll
+        for (int y = 0; y < EB; ++y) o[y * EB] = out[y];
+      }
+      __syncthreads();
+      // along z, into the box: one task per (quantity, y, x)
+      for (int t = tid; t < NV * EB * EB; t += BLOCK) {
+        const int i = t % EB, y = (t / EB) % EB, v = t / (EB * EB);
+        double x[3][n];
+#pragma unroll
+        for (int g = 0; g < 3; ++g)
+#pragma unroll
+          for (int k = 0; k < n; ++k) x[g][k] = rb[((v * 3 + g) * n + k) * EB * EB + y * EB + i];
+        const double sgn[2] = {v == 3 && wall[2][0] ? -1.0 : 1.0, v == 3 && wall[2][1] ? -1.0 : 1.0};
+        double out[EB];
+        lim_extend<n>(x[1], x[0], x[2], mir[2], sgn, out);
+#pragma unroll
+        for (int z = 0; z < EB; ++z) box[v * NB + (z * EB + y) * EB + i] = out[z];
+      }
+    } else {
+      // along y, into registers (the box takes the place of the projection
+      // along x), then the box: one task per (quantity, x)
+      double out[EB];
+      const int t = tid, i = t % EB, v = t / EB;
+      static_assert(NV * EB <= BLOCK || DIM == 3, "one task per thread");
+      if (t < NV * EB) {
+        double x[3][n];
+#pragma unroll
+        for (int g = 0; g < 3; ++g)
+#pragma unroll
+          for (int k = 0; k < n; ++k) x[g][k] = ra[((v * NOY + g) * n + k) * EB + i];
+        const double sgn[2] = {v == 2 && wall[1][0] ? -1.0 : 1.0, v == 2 && wall[1][1] ? -1.0 : 1.0};
+        lim_extend<n>(x[1], x[0], x[2], mir[1], sgn, out);
+      }
+      __syncthreads();
+      if (t < NV * EB) {
+#pragma unroll
+        for (int y = 0; y < EB; ++y) box[v * NB + y * EB + i] = out[y];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < GL::PPT; ++j)
+      if (sgn_of[j] >= 0) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+          box[v * NB + tid + j * BLOCK] = v >= 1 && v <= DIM && ((sgn_of[j] >> (v - 1)) & 1) ? -pre[j][v] : pre[j][v];
+      }
     __syncthreads();
     // 2. minmod slopes, extrapolated values and their half-step correction
     //    for the cell's subcells and the first ghost layer across each face
@@ -653,17 +806,19 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
           ext[d][0][v] = wv - 0.5 * slope;
           ext[d][1][v] = wv + 0.5 * slope;
         }
-        ok = ok && PDE::admissible(ext[d][0], ext[d][0], a.pde) && PDE::admissible(ext[d][1], ext[d][1], a.pde);
+        // (finite values: tested below, a moved value is finite only if its extrapolated one is)
+        ok = ok && lim_admissible<PDE, false>(ext[d][0], a.pde) && lim_admissible<PDE, false>(ext[d][1], a.pde);
       }
 #pragma unroll
       for (int v = 0; v < NV; ++v) cv[v] = 0.0;
 #pragma unroll
       for (int d = 0; d < DIM; ++d) {
-        double Fl[DIM][NV], Fr[DIM][NV];
-        PDE::fluxes(ext[d][0], ext[d][0], a.pde, Fl);
-        PDE::fluxes(ext[d][1], ext[d][1], a.pde, Fr);
+        double Fl[NV], Fr[NV];
+        PDE::flux_dir(ext[d][0], ext[d][0], a.pde, d, Fl);
+        PDE::flux_dir(ext[d][1], ext[d][1], a.pde, d, Fr);
+        const double s = 0.5 * dt * ihs[d];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) cv[v] += 0.5 * dt / hs[d] * (Fl[d][v] - Fr[d][v]);
+        for (int v = 0; v < NV; ++v) cv[v] += s * (Fl[v] - Fr[v]);
       }
 #pragma unroll
       for (int d = 0; d < DIM; ++d)
@@ -672,14 +827,39 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
           double mv[NV];
 #pragma unroll
           for (int v = 0; v < NV; ++v) mv[v] = ext[d][side][v] + cv[v];
-          ok = ok && PDE::admissible(mv, mv, a.pde);
+          ok = ok && lim_admissible<PDE>(mv, a.pde);
         }
 #pragma unroll
       for (int v = 0; v < NV; ++v) corr[v * NC + q] = cv[v];
       okf[q] = ok ? 1 : 0;
     }
     __syncthreads();
-    // 3. Rusanov at the subcell faces and the update of the cell's subcells
+    // 3. Rusanov at every subface (components rotated so that the normal
+    //    momentum is component 1), then the update of the cell's subcells
+    for (int f = tid; f < DIM * GL::NFC; f += BLOCK) {
+      const int d = f / GL::NFC, fd = f - d * GL::NFC;
+      const int i = fd % (m + 1), t = fd / (m + 1), t0 = t % m, t1 = t / m;
+      // the subcell above the face (index i along d), its box and correction
+      // positions; t: the other axes, lower first
+      const int x[3] = {d == 0 ? i : t0, d == 0 ? t0 : (d == 1 ? i : t1), d == 2 ? i : t1};
+      const int p = (x[0] + 2) + EB * ((x[1] + 2) + (DIM == 3 ? EB * (x[2] + 2) : 0));
+      const int q = (x[0] + 1) + EC * ((x[1] + 1) + (DIM == 3 ? EC * (x[2] + 1) : 0));
+      const int sd = d == 0 ? 1 : (d == 1 ? EB : EB * EB), cd = d == 0 ? 1 : (d == 1 ? EC : EC * EC);
+      int cv[NV];
+      cv[0] = 0;
+      cv[NV - 1] = NV - 1;
+#pragma unroll
+      for (int e = 0; e < DIM; ++e) cv[1 + e] = 1 + (d + e < DIM ? d + e : d + e - DIM);
+      double e0[NV], e1[NV], G[NV];
+      lim_moved<PDE, N>(box, corr, okf, p - sd, q - cd, sd, 1, cv, e0);
+      lim_moved<PDE, N>(box, corr, okf, p, q, sd, 0, cv, e1);
+      lim_rusanov<PDE>(a.pde, e0, e1, G);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) ff[f * NV + cv[v]] = G[v];
+    }
+    __syncthreads();
+    // (the threads past the subcells: the next cell's neighbourhood)
+    neighbourhood(it + gridDim.x, BLOCK - 64);
     double vnew[GL::VPT][NV];
 #pragma unroll
     for (int j = 0; j < GL::VPT; ++j) {
@@ -687,37 +867,16 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
       if (s >= NS) break;
       int x[3];
       lim_multi<DIM>(s, m, x);
-      int p = 0, q = 0, mb = 1, mc = 1;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        p += (x[d] + 2) * mb;
-        q += (x[d] + 1) * mc;
-        mb *= EB;
-        mc *= EC;
-      }
+      const int p = (x[0] + 2) + EB * ((x[1] + 2) + (DIM == 3 ? EB * (x[2] + 2) : 0));
       double acc[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) acc[v] = 0.0;
 #pragma unroll
       for (int d = 0; d < DIM; ++d) {
-        const int sd = d == 0 ? 1 : (d == 1 ? EB : EB * EB), cd = d == 0 ? 1 : (d == 1 ? EC : EC * EC);
-        double e0[NV], e1[NV], Ghi[NV], Glo[NV];
-        lim_moved<PDE, N>(box, corr, okf, p, q, d, 1, e0);
-        lim_moved<PDE, N>(box, corr, okf, p + sd, q + cd, d, 0, e1);
-        lim_rusanov<PDE>(a.pde, d, e0, e1, Ghi);
-        lim_moved<PDE, N>(box, corr, okf, p - sd, q - cd, d, 1, e0);
-        lim_moved<PDE, N>(box, corr, okf, p, q, d, 0, e1);
-        lim_rusanov<PDE>(a.pde, d, e0, e1, Glo);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] += (Ghi[v] - Glo[v]) / hs[d];
-        // subface index across the other axes, lower axis fastest
         const int t = DIM == 2 ? x[1 - d] : (d == 0 ? x[1] + m * x[2] : (d == 1 ? x[0] + m * x[2] : x[0] + m * x[1]));
-        if (x[d] == m - 1)
+        const double* g = ff + (d * GL::NFC + t * (m + 1) + x[d]) * NV;
 #pragma unroll
-          for (int v = 0; v < NV; ++v) fsub[((2 * d + 1) * NSF + t) * NV + v] = Ghi[v];
-        if (x[d] == 0)
-#pragma unroll
-          for (int v = 0; v < NV; ++v) fsub[((2 * d) * NSF + t) * NV + v] = Glo[v];
+        for (int v = 0; v < NV; ++v) acc[v] += (g[NV + v] - g[v]) * ihs[d];
       }
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -727,7 +886,10 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
     }
     __syncthreads();
     // 4. back to the DG space, and the face-node fluxes for DG neighbours
-    double* vn = box;
+    double* const vn = ra;                  // [v][subcell]
+    double* const r1 = ra + NV * NS;        // fit: [v][(sz)][sy][kx]
+    double* const r2 = corr;                // fit, 3-D: [v][sz][ky][kx]
+    double* const g1 = r1 + NV * ipow(m, DIM - 1) * n;  // face fluxes, 3-D: [face][v][t1][f0]
 #pragma unroll
     for (int j = 0; j < GL::VPT; ++j) {
       const int s = tid + j * BLOCK;
@@ -735,13 +897,29 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
 #pragma unroll
         for (int v = 0; v < NV; ++v) vn[v * NS + s] = vnew[j][v];
     }
+    // subfaces of the cell's face (side i = 0 or m), along their first axis:
+    // one task per (face, quantity, t1), all n face nodes
+    constexpr int NT1 = DIM == 3 ? m : 1;
+    for (int t = tid; t < 2 * DIM * NV * NT1; t += BLOCK) {
+      const int t1 = t % NT1, v = (t / NT1) % NV, face = t / (NT1 * NV);
+      if (!dgface[face]) continue;
+      const double* g = ff + ((face >> 1) * GL::NFC + t1 * m * (m + 1) + (face & 1) * m) * NV + v;
+      double in[m];
+#pragma unroll
+      for (int j = 0; j < m; ++j) in[j] = g[j * (m + 1) * NV];
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        double acc = 0.0;
+#pragma unroll
+        for (int j = 0; j < m; ++j) acc += LC::Qf[k][j] * in[j];
+        if constexpr (DIM == 3) g1[t * n + k] = acc;
+        else w.gfv[((c * 2 * DIM + face) * NV + v) * F + k] = acc;
+      }
+    }
     __syncthreads();
     // least-squares fit, one axis at a time: x (vn -> r1), y (r1 -> r2,
     // 3-D), the last axis into Q
     {
-      using LC = LimConst<n>;
-      double* r1 = box + NV * NS;  // [v][(sz)][sy][kx]
-      double* r2 = corr;           // 3-D: [v][sz][ky][kx]
       constexpr int L1 = NV * ipow(m, DIM - 1);
       for (int line = tid; line < L1; line += BLOCK) {
         double in[m];
@@ -753,6 +931,23 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
 #pragma unroll
           for (int j = 0; j < m; ++j) acc += LC::B[k][j] * in[j];
           r1[line * n + k] = acc;
+        }
+      }
+      if constexpr (DIM == 3) {
+        // (meanwhile) the face fluxes along their second axis
+        for (int t = tid; t < 2 * DIM * NV * n; t += BLOCK) {
+          const int f0 = t % n, v = (t / n) % NV, face = t / (n * NV);
+          if (!dgface[face]) continue;
+          double in[m];
+#pragma unroll
+          for (int j = 0; j < m; ++j) in[j] = g1[((face * NV + v) * m + j) * n + f0];
+#pragma unroll
+          for (int k = 0; k < n; ++k) {
+            double acc = 0.0;
+#pragma unroll
+            for (int j = 0; j < m; ++j) acc += LC::Qf[k][j] * in[j];
+            w.gfv[((c * 2 * DIM + face) * NV + v) * F + k * n + f0] = acc;
+          }
         }
       }
       __syncthreads();
@@ -788,18 +983,6 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
           Q[c * NV * S + v * S + k * RL + r] = acc;
         }
       }
-    }
-    for (int i = tid; i < 2 * DIM * NV * F; i += BLOCK) {
-      const int f = i % F, v = (i / F) % NV, face = i / (F * NV);
-      const int f0 = f % n, f1 = f / n;
-      double acc = 0.0;
-      for (int t = 0; t < NSF; ++t) {
-        const int t0 = t % m, t1 = t / m;
-        double qv = Qf[f0 * m + t0];
-        if (DIM == 3) qv *= Qf[f1 * m + t1];
-        acc += qv * fsub[(face * NSF + t) * NV + v];
-      }
-      w.gfv[((c * 2 * DIM + face) * NV + v) * F + f] = acc;
     }
   }
 }
@@ -885,7 +1068,7 @@ lim_lambda_kernel(const KArgs a, const double* __restrict__ Q, const double* __r
 template <class PDE, int N>
 struct LimLaunch {
   using GL = GeoLim<PDE, N>;
-  static constexpr int kFvGrid = 512, kFaceGrid = 1024;
+  static constexpr int kFaceGrid = 1024;
   // prepare; the caller's DG step follows
   static hipError_t before(const KArgs& a, const double* Q, const double* sub_in, const uint8_t* status,
                            const LimWork& w, hipStream_t st) {
@@ -905,8 +1088,8 @@ struct LimLaunch {
     hipLaunchKernelGGL((lim_classify_kernel<GL::DIM>), dim3((unsigned)((a.ncells + 255) / 256)), dim3(256), 0, st,
                        a, status, w);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((lim_fv_kernel<PDE, N>), dim3(kFvGrid), dim3(GL::BLOCK), 0, st, a, clock, sub_in, Q,
-                       sub_out, w);
+    hipLaunchKernelGGL((lim_fv_kernel<PDE, N>), dim3(GL::FV_GRID), dim3(GL::BLOCK), 0, st, a, clock, sub_in, Q,
+                       sub_out, status, w);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL((lim_faces_kernel<PDE, N>), dim3(kFaceGrid), dim3(256), 0, st, a, clock, traces,
                        status, Q, w);
