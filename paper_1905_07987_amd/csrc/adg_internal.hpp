@@ -88,6 +88,11 @@ struct KArgs {
   // by the adjoint step instead of recomputing them; [C][keep slots][S]
   // doubles (see adg_keep_size).  Null in every other launch.
   double* keep;
+  // limited steps: the FP64 predictor copies u^n here ([C][nvar][S]; null:
+  // not), the corrector stores the largest signal speed of every cell's new
+  // nodal values here ([C]; null: not)
+  double* qcopy;
+  double* cell_lam;
 };
 
 // Workspace of a step with the a-posteriori subcell limiter (owned by the
@@ -97,10 +102,16 @@ struct LimWork {
   double* Qold;       // [C][nv][S]   u^n
   uint8_t* st_prev;   // [C]          status at the start of the step
   uint8_t* trb;       // [C]          troubled flags of this step
-  double* lohi;       // [C][nv][2]   range of the subcell averages at t^n
-  double* lohi_next;  // [C][nv][2]   range of the candidate's subcell averages (detect)
-  int reuse;          // prepare takes lohi_next of DG cells (status 0) instead of projecting
-  int store_next;     // detect writes lohi_next
+  // [2][C][nv][2]: the range of the subcell averages at t^n (array *parity)
+  // and of the candidate's (the other one; detect).  A step that stores the
+  // latter turns *parity (on the device, so a captured step stays valid), and
+  // they are the ranges at t^n of the next step's untouched DG cells.
+  double* lohi2;
+  int* parity;
+  int reuse;          // prepare leaves the ranges of DG cells (status 0) as stored
+  int store_next;     // detect stores the candidate's ranges, classify turns parity
+  int copy;           // prepare copies u^n to Qold (else the predictor does)
+  double* cell_lam;   // [C]  largest signal speed of the candidate's nodes (corrector)
   int* fv_list;       // [C]
   int* y_list;        // [C]
   int* counters;      // [4]: troubled cells, FV cells, DG cells with FV faces
@@ -144,6 +155,8 @@ struct KernelSet {
   hipError_t (*bc_flux)(const KArgs&, double* bc_trace, hipStream_t);
   // doubles per node of KArgs::keep (0 where the adjoint is not built)
   int keep_slots;
+  // whether predict(precision) writes KArgs::qcopy
+  bool (*copies_state)(int precision);
 };
 
 // Registries implemented by the per-PDE translation units; return nullptr if

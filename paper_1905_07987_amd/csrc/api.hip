@@ -657,8 +657,8 @@ adg_status adg_limiter_reserve(adg_ctx* ctx) {
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t ntab = (size_t)3 * m * n;
     const size_t sz[10] = {up(ntab * 8), up((size_t)C * nv * S * 8), up((size_t)C), up((size_t)C),
-                           up((size_t)C * nv * 2 * 8), up((size_t)C * 4), up((size_t)C * 4), up(4 * 4),
-                           up((size_t)C * 2 * ctx->dim * nv * ctx->F * 8), up((size_t)C * nv * 2 * 8)};
+                           up((size_t)C * nv * 4 * 8), up((size_t)C * 4), up((size_t)C * 4), up(4 * 4 + 4),
+                           up((size_t)C * 2 * ctx->dim * nv * ctx->F * 8), up((size_t)C * 8)};
     size_t total = 0;
     for (size_t b : sz) total += b;
     void* blk = nullptr;
@@ -669,6 +669,10 @@ adg_status adg_limiter_reserve(adg_ctx* ctx) {
       return fail(ADG_ERR_INVALID_ARG, "limiter tables failed");
     }
     hipError_t e = hipMemcpy(blk, tab.data(), ntab * 8, hipMemcpyHostToDevice);
+    size_t cnt_at = 0;  // the counters, then the parity of the range arrays
+    for (int i = 0; i < 7; ++i) cnt_at += sz[i];
+    if (e == hipSuccess) e = hipMemset((char*)blk + cnt_at, 0, sz[7]);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
       (void)hipFree(blk);
       return hip_fail(e, "limiter tables upload");
@@ -679,12 +683,13 @@ adg_status adg_limiter_reserve(adg_ctx* ctx) {
     w.Qold = (double*)p;        p += sz[1];
     w.st_prev = (uint8_t*)p;    p += sz[2];
     w.trb = (uint8_t*)p;        p += sz[3];
-    w.lohi = (double*)p;        p += sz[4];
+    w.lohi2 = (double*)p;       p += sz[4];
     w.fv_list = (int*)p;        p += sz[5];
     w.y_list = (int*)p;         p += sz[6];
-    w.counters = (int*)p;       p += sz[7];
+    w.counters = (int*)p;
+    w.parity = (int*)p + 4;     p += sz[7];
     w.gfv = (double*)p;         p += sz[8];
-    w.lohi_next = (double*)p;
+    w.cell_lam = (double*)p;
     ctx->lim_block = blk;
     ctx->lim_ranges_stored = false;
     ctx->lim_bytes = total;
@@ -714,13 +719,18 @@ adg_status adg_step_limited(adg_ctx* ctx, double* Q, double* clock, const double
   LimWork w = ctx->lim;
   w.reuse = reuse_flag && ctx->lim_ranges_stored ? 1 : 0;
   w.store_next = reuse_flag ? 1 : 0;
+  w.copy = ctx->ks->copies_state(ctx->cfg.precision) ? 0 : 1;
   ctx->lim_ranges_stored = false;
   hipError_t e = ctx->ks->lim_before(ctx->args, Q, sub_in, status, w, s);
   if (e != hipSuccess) return hip_fail(e, "limiter prepare launch");
-  e = k_predict(ctx, Q, nullptr, clock, Q, ctx->traces, 0, s);
+  KArgs a = ctx->args;
+  if (!w.copy) a.qcopy = w.Qold;
+  e = ctx->ks->predict(a, ctx->cfg.precision, Q, nullptr, clock, Q, ctx->traces, 0, s);
   if (e != hipSuccess) return hip_fail(e, "predict launch");
   ctx->traces_ready = true;
-  e = k_correct(ctx, Q, nullptr, clock, 0, s);
+  a = ctx->args;
+  if (flags & ADG_STEP_NEXT_DT) a.cell_lam = w.cell_lam;
+  e = ctx->ks->correct(a, Q, nullptr, clock, ctx->traces, 0, s);
   if (e != hipSuccess) return hip_fail(e, "correct launch");
   e = ctx->ks->lim_after(ctx->args, Q, clock, ctx->traces, sub_in, sub_out, status, w,
                          (flags & ADG_STEP_NEXT_DT) ? 1 : 0, s);

@@ -2007,9 +2007,25 @@ correct_kernel(const KArgs a, double* __restrict__ Q, const double* __restrict__
       qn[v] = (PDE::kLinear ? qold[v] : Q[idx]) - surf[v];
       Q[idx] = qn[v];
     }
-    if (next_dt) {
+    if (next_dt || (!PDE::kLinear && a.cell_lam)) {
 #pragma unroll
       for (int d = 0; d < DIM; ++d) lam = lam_max(lam, PDE::max_eigen(qn, P, a.pde, d));
+    }
+  }
+  if constexpr (!PDE::kLinear) {
+    if (a.cell_lam) {
+      // per-cell maxima: eight lanes fold a cell's nodes
+      red[tid] = lam;
+      __syncthreads();
+      for (int t = tid; t < CPB * 8; t += BLOCK) {
+        const int c2 = t >> 3;
+        double x = 0.0;
+        for (int i = t & 7; i < S; i += 8) x = lam_max(x, red[c2 * S + i]);
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) x = lam_max(x, __shfl_xor(x, off, 64));
+        if ((t & 7) == 0 && cell0 + c2 < ncells) a.cell_lam[cell0 + c2] = x;
+      }
+      __syncthreads();
     }
   }
   if (next_dt) {
@@ -2433,11 +2449,14 @@ struct Launch {
     hipLaunchKernelGGL((bc_flux_kernel<PDE, N>), dim3(1), dim3(64), 0, st, a, tr);
     return hipGetLastError();
   }
+  static bool copies_state(int precision) {
+    return !PDE::kLinear && precision == ADG_FP64 && (Ch::kN64 || Ch::kLineAlways);
+  }
   static const KernelSet* set() {
     static const KernelSet ks = {GP::BLOCK, GP::CPB, GB::CPB,
                                  &predict, &correct, &stable_dt, &admissible, adjoint_entry(),
                                  step_fused_entry(), lim_before_entry(), lim_after_entry(), &bc_flux,
-                                 GeoAdjL<PDE, N>::supported ? KeepGeo<PDE, N>::SLOTS : 0};
+                                 GeoAdjL<PDE, N>::supported ? KeepGeo<PDE, N>::SLOTS : 0, &copies_state};
     return &ks;
   }
 };

@@ -797,6 +797,7 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const double un = Q[(cell * NV + v) * S + k];
+      if (a.qcopy) a.qcopy[(cell * NV + v) * S + k] = un;
       Qout[(cell * NV + v) * S + k] = un + dt * (Sbar[v] - divF[v] - Nbar[v]);
     }
   }

@@ -467,12 +467,21 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
     }
   }
   if (active) {
-    const double* Qc = Q0c + opaque_zero();
-    double* const Qo = Qout + cell * (long long)(NV * S) + l;
+    double un[n][NV];
+    load_u(un);
+    const long long c0 = cell * (long long)(NV * S) + l;
+    if (a.qcopy) {
+      // (a limited step's copy of u^n)
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int z = 0; z < n; ++z) a.qcopy[c0 + v * S + z * F] = un[z][v];
+    }
+    double* const Qo = Qout + c0;
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-      for (int z = 0; z < n; ++z) Qo[v * S + z * F] = fma_r(dt, vol[z][v], Qc[v * S + z * F]);
+      for (int z = 0; z < n; ++z) Qo[v * S + z * F] = fma_r(dt, vol[z][v], un[z][v]);
   }
 }
 
