@@ -282,7 +282,10 @@ struct GeoAdjL {
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
   // rows of L^T with the forward-gradient channels, qbar, gradient partials
-  static constexpr int CELL_ELEMS = cmax(cmax((C::NCH + G::DIM * C::ngrad()) * LinLayout<G>::SP, G::NV * G::S),
+  using LG = LinGather<PDE, N, double>;
+  static constexpr int ROW_ELEMS = LG::on ? LG::SETS * LG::ROWS_T * G::S
+                                          : (C::NCH + G::DIM * C::ngrad()) * LinLayout<G>::SP;
+  static constexpr int CELL_ELEMS = cmax(cmax(ROW_ELEMS, G::NV * G::S),
                                          G::S * (G::NP > 0 ? G::NP : 1));
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
   static constexpr int by_lds = cmax(1, (76 * 1024) / (CELL_ELEMS * 8));
@@ -327,6 +330,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
   const bool active = cell < a.ncells;
   const long long cl = active ? cell : a.ncells - 1;  // clamp loads of the ragged tail
   double* const mine = lds + lc * GA::CELL_ELEMS;
+  typename Op::Lane line = Op::lane_data(a, k, tid);
 
   const double t_n = clock[0], dt = clock[1];
   const int I = a.picard_iters;
@@ -388,7 +392,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
 #pragma unroll
         for (int c = 0; c < NGX; ++c) fwv[kk][c] = c < NGR ? t[C::grad_var(c)] : 0.0;
         double Lt[NV], g[DIM][NV];
-        Op::apply(a, lds, mine, pk, tid, t, P, inv_h, Lt, g);
+        Op::apply(a, lds, mine, pk, tid, line, t, P, inv_h, Lt, g);
         const double ck = a.lin_c[kk];
 #pragma unroll
         for (int v = 0; v < NV; ++v) t[v] = ck * u[v] + dt * Lt[v];
@@ -445,7 +449,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
     double fq[NGX], gq[DIM][NV];
 #pragma unroll
     for (int c = 0; c < NGX; ++c) fq[c] = c < NGR ? t[C::grad_var(c)] : 0.0;
-    Op::template apply_T<true>(a, lds, mine, pk, tid, nu, P, inv_h, mu, fq, gq);
+    Op::template apply_T<true>(a, lds, mine, pk, tid, line, nu, P, inv_h, mu, fq, gq);
     param_terms(gq, nu, gp);
   }
 #pragma unroll
@@ -462,7 +466,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
         nu[v] = dt * mu[v];
       }
       double gq[DIM][NV];
-      Op::template apply_T<true>(a, lds, mine, pk, tid, nu, P, inv_h, mu, fwv[kk], gq);
+      Op::template apply_T<true>(a, lds, mine, pk, tid, line, nu, P, inv_h, mu, fwv[kk], gq);
       param_terms(gq, nu, gp);
     }
   }

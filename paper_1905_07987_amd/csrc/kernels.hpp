@@ -57,6 +57,9 @@ struct Geo {
 __device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+template <class... T>
+using kern_void_t = void;
+
 // Derivative channels per direction: the nonzero flux components, then the
 // quantities whose gradient feeds the non-conservative product.
 template <class PDE>
@@ -1253,11 +1256,74 @@ struct LinLayout {
   static constexpr int SP = G::F * lay_A(0);  // elements per row (every line, A_d the same)
 };
 
+// PDEs linear in Q whose flux components are components of the state (trait
+// kFluxCopies), FP64, 3-D: the derivatives are gathered instead of taken by
+// line tasks (LinGather below).
+template <class P, class = void>
+struct FluxCopies {
+  static constexpr bool value = false;
+};
+template <class P>
+struct FluxCopies<P, kern_void_t<decltype(P::kFluxCopies)>> {
+  static constexpr bool value = P::kFluxCopies;
+};
+
+// Which of the linear predictor's derivatives are gathered, and the LDS rows
+// (of the S nodes of a cell, in node order) that takes.
+//
+// A line task's derivative costs the LDS four accesses per value (the value
+// written, read by the task, the result written and read back), and an 8-byte
+// write takes 6.2 cycles of the CU per wave against 2.3 for a read.  Where
+// the fluxes are components of the state, a component is written once for
+// every direction and every node reads the others of its line: one L
+// application of elasticity takes 9 writes and 18 n reads per node instead of
+// 36 and 36, and one barrier instead of two (the rows alternate between two
+// sets).  At n = 4 a cell is one wave with node x + 4 y + 16 z on its lane,
+// and v_mfma_f64_4x4x4 contracts along z in place: 8 writes and 36 reads.
+// Measured, one predictor: N = 2, 45 x 38 x 29 cells 147 -> 91 us (4.3 TB/s);
+// N = 3 with the step's keep buffer, 32^3 cells 171 -> 140 us (6.2 TB/s,
+// mostly writes); its adjoint 317 -> 228 us.  Orders 1 to 3: at N = 4 the
+// gather takes 5 multiplications per derivative against 2.6 of the even-odd
+// line tasks, and 168 registers leave 3 waves per SIMD (a step of 48^3
+// cells 1.48 -> 2.5 ms).
+template <class PDE, int N, class R>
+struct LinGather {
+  using C = Chan<PDE>;
+  static constexpr int n = N + 1, NV = PDE::NV, DIM = PDE::DIM;
+  static constexpr bool on = FluxCopies<PDE>::value && DIM == 3 && n <= 4 && std::is_same<R, double>::value;
+  static constexpr bool ZM = n == 4;          // the last axis on the matrix cores
+  static constexpr bool ROT = n == 2 || n == 4;  // see deriv() of LinOp
+  static constexpr int XD = ZM ? 2 : 3;       // axes whose derivatives are gathered
+  static constexpr int SETS = ZM ? 1 : 2;     // row sets (a wave's own rows need no barrier)
+  // row of state component v among those L t gathers (-1: not gathered)
+  static constexpr bool used(int v) {
+    if constexpr (on) {
+      if (PDE::grad_needed(v)) return true;
+      for (int d = 0; d < XD; ++d)
+        for (int c = 0; c < C::NFLUX; ++c)
+          if (PDE::flux_of(d, C::flux_var(d, c)) == v) return true;
+    }
+    return false;
+  }
+  static constexpr int row(int v) {
+    int r = 0;
+    for (int i = 0; i < v; ++i) r += used(i) ? 1 : 0;
+    return r;
+  }
+  static constexpr int ROWS = row(NV);
+  // rows of L^T: the adjoint's flux components, the gradient adjoints of
+  // every gathered axis, the forward gradient quantities
+  static constexpr int NGR = C::ngrad(), NFL = C::NFLUX;
+  static constexpr int ROWS_T = (XD * NFL) + XD * NGR + NGR;
+};
+
 template <class PDE, int N, class R>
 struct GeoL {
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
-  static constexpr int ROW_ELEMS = C::NCH * LinLayout<G>::SP;  // every derivative channel of one field
+  using LG = LinGather<PDE, N, R>;
+  // every derivative channel of one field
+  static constexpr int ROW_ELEMS = LG::on ? LG::SETS * LG::ROWS * G::S : C::NCH * LinLayout<G>::SP;
   static constexpr int AVG_ELEMS = G::NV * G::S;    // the time average in node order
   static constexpr int CELL_ELEMS = cmax(ROW_ELEMS, AVG_ELEMS);
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
@@ -1329,6 +1395,58 @@ struct LinOp {
   // wave and a wave-level fence replaces the block barrier (LDS accesses of
   // one wave complete in order).
   static constexpr bool kWave = G::S == 64;
+  using LG = LinGather<PDE, N, R>;
+  // the operator's matrices as this node needs them
+  struct Lane {
+    static constexpr int XD = LG::XD;
+    double c[XD][n];   // the node's row of D / h of axis d
+    double ct[XD][n];  // and of its transpose (only L^T reads it)
+    int at[XD];        // the line's first node (see deriv)
+    int rot[XD][n];    // or the node r further (cyclic)
+    double mz, mzt;    // n = 4: the element of D / h of the last axis, as a matrix operand
+    int set;           // row set of the next application
+  };
+  __device__ static __forceinline__ Lane lane_data(const KArgs& a, int k, int tid) {
+    Lane L;
+    if constexpr (LG::on) {
+      const int pos[3] = {k % n, (k / n) % n, k / (n * n)}, stride[3] = {1, n, n * n};
+#pragma unroll
+      for (int d = 0; d < LG::XD; ++d) {
+        L.at[d] = k - pos[d] * stride[d];
+#pragma unroll
+        for (int r = 0; r < n; ++r) {
+          const int p = !LG::ROT ? r : (pos[d] + r < n ? pos[d] + r : pos[d] + r - n);
+          L.rot[d][r] = L.at[d] + p * stride[d];
+          L.c[d][r] = a.inv_h[d] * a.t64.D[pos[d]][p];
+          L.ct[d][r] = a.inv_h[d] * a.t64.D[p][pos[d]];
+        }
+      }
+      const int i = tid & 3, kk = (tid >> 4) & 3;
+      L.mz = a.inv_h[2] * a.t64.D[i < n ? i : 0][kk < n ? kk : 0];
+      L.mzt = a.inv_h[2] * a.t64.D[kk < n ? kk : 0][i < n ? i : 0];
+      L.set = 0;
+    }
+    return L;
+  }
+  // sum over the line of c times the row's values.  Where the nodes of a cell
+  // fill whole groups of lanes (ROT: n = 2, 4) every lane starts from its own
+  // value and reads the others, r places further: a permutation of the lane's
+  // neighbours, so no two lanes of a half wave share a bank.  Otherwise all
+  // lanes of a line read the same node at a time (one access, broadcast).
+  __device__ static __forceinline__ double deriv(const Lane& L, const double* row, int d, const double (&c)[n],
+                                                 double own) {
+    double s = LG::ROT ? c[0] * own : c[0] * row[L.at[d]];
+    const int st = d == 0 ? 1 : (d == 1 ? n : n * n);
+#pragma unroll
+    for (int r = 1; r < n; ++r) s = fma_r(c[r], LG::ROT ? row[L.rot[d][r]] : row[L.at[d] + r * st], s);
+    return s;
+  }
+  // A t of the last axis, t on the lanes of a cell of 4^3 nodes: lane
+  // i + 4 b + 16 k holds A[i][k] and t[k][i] of block b, and element [k][i]
+  // of the result.
+  __device__ static __forceinline__ double along_z(double A, double t) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(A, t, 0.0, 0, 0, 0);
+  }
 
   __device__ static __forceinline__ void sync() {
     if constexpr (kWave) {
@@ -1354,8 +1472,12 @@ struct LinOp {
   // out = L t = S(t) - div F(t) - B(t) grad t at this node; g = the gradients
   // the non-conservative product reads (zero elsewhere)
   __device__ static __forceinline__ void apply(const KArgs& a, R* lds, R* mine, const int (&pk)[DIM],
-                                               int tid, const R (&t)[NV], const R* P,
+                                               int tid, Lane& ln, const R (&t)[NV], const R* P,
                                                const R (&inv_h)[3], R (&out)[NV], R (&g)[DIM][NV]) {
+    if constexpr (LG::on) {
+      apply_gather(a, mine, ln, tid % G::S, t, P, out, g);
+      return;
+    }
     R Fl[DIM][NV];
     PDE::fluxes(t, P, a.pde, Fl);
 #pragma unroll
@@ -1366,17 +1488,28 @@ struct LinOp {
       for (int cc = 0; cc < NGR; ++cc) mine[(d * NCHD + NFL + cc) * SP + pk[d]] = t[C::grad_var(cc)];
     }
     sync();
-    cell_tasks<NCH * F>(tid, [&](int c2, int t) {
-      const int l = t % F, ch = t / F;
-      const int d = ch / NCHD, st = LL::lay_B(d);
-      R* row = lds + c2 * CELL_ELEMS + ch * SP + LL::addr(d, l, 0);
+    auto line = [&](R* row) {
       R x[n], y[n];
 #pragma unroll
-      for (int m = 0; m < n; ++m) x[m] = row[m * st];
+      for (int m = 0; m < n; ++m) x[m] = row[m];
       line_deriv<R, n>(x, y, R(1));
 #pragma unroll
-      for (int i = 0; i < n; ++i) row[i * st] = y[i];
-    });
+      for (int i = 0; i < n; ++i) row[i] = y[i];
+    };
+    if constexpr (CELL_ELEMS == NCH * SP) {
+      // the lines of every cell, channel and direction follow one another at
+      // the line stride: task i is line i (kWave: of the wave's cell).  (The
+      // cell, channel and direction of a task worked out instead: 3 % slower
+      // at elastic N = 4.)
+      constexpr int NT = NCH * F * (kWave ? 1 : CPB), W = kWave ? 64 : BLOCK;
+      const int first = kWave ? tid & 63 : tid;
+      R* const row = (kWave ? lds + (tid >> 6) * CELL_ELEMS : lds) + first * LL::lay_A(0);
+#pragma unroll
+      for (int i = 0; i < NT; i += W)
+        if (i + W <= NT || first < NT - i) line(row + i * LL::lay_A(0));
+    } else {
+      cell_tasks<NCH * F>(tid, [&](int c2, int t) { line(lds + c2 * CELL_ELEMS + t * LL::lay_A(0)); });
+    }
     sync();
     // the 1/h of each direction is applied here; the divergence starts at
     // the first direction with a flux in v
@@ -1419,6 +1552,104 @@ struct LinOp {
     // next calls sync() first.
   }
 
+  // The same with the derivatives gathered.
+  __device__ static __forceinline__ void apply_gather(const KArgs& a, double* mine, Lane& ln, int k,
+                                                      const double (&t)[NV], const double* P, double (&out)[NV],
+                                                      double (&g)[DIM][NV]) {
+    constexpr int S = G::S;
+    double* const rows = mine + ln.set * (LG::ROWS * S);
+    if constexpr (LG::SETS == 2) ln.set ^= 1;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      if (LG::used(v)) rows[LG::row(v) * S + k] = t[v];
+    sync();
+    double divF[NV], B[NV], Sv[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      divF[v] = Sv[v] = B[v] = 0.0;
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        g[d][v] = 0.0;
+        const int f = PDE::flux_nonzero(d, v) ? PDE::flux_of(d, v) : 0;
+        if (PDE::flux_nonzero(d, v))
+          divF[v] += d < LG::XD ? deriv(ln, rows + LG::row(f) * S, d, ln.c[d < LG::XD ? d : 0], t[f])
+                                : along_z(ln.mz, t[f]);
+        if (PDE::grad_needed(v))
+          g[d][v] = d < LG::XD ? deriv(ln, rows + LG::row(v) * S, d, ln.c[d < LG::XD ? d : 0], t[v])
+                               : along_z(ln.mz, t[v]);
+      }
+    }
+    if constexpr (PDE::kHasNcp) PDE::ncp(t, P, a.pde, g, B);
+    if constexpr (PDE::kHasSource) PDE::source(t, P, a.pde, Sv);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v] = PDE::kHasSource ? Sv[v] - divF[v] - B[v] : -divF[v] - B[v];
+  }
+
+  // L^T nu (and, FW, the gradients of fw) with the derivatives gathered.
+  template <bool FW>
+  __device__ static __forceinline__ void apply_T_gather(const KArgs& a, double* mine, Lane& ln, int k,
+                                                        const double (&nu)[NV], const double* P, double (&mu)[NV],
+                                                        const double* fw, double (&gq)[DIM][NV]) {
+    constexpr int S = G::S, XD = LG::XD, LX = XD - 1;
+    double* const rows = mine + ln.set * (LG::ROWS_T * S);
+    if constexpr (LG::SETS == 2) ln.set ^= 1;
+    double lB[NV], lG[DIM][NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      lB[v] = -nu[v];
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) lG[d][v] = 0.0;
+    }
+    if constexpr (PDE::kHasNcp) PDE::ncp_T(P, a.pde, lB, lG);
+    // rows: a flux component of every gathered axis whose variable another
+    // axis has not written yet, the gradient adjoints, the forward quantities
+    auto flux_row = [](int d, int cc) {
+      for (int e = 0; e < d; ++e)
+        if (C::flux_var(e, cc) == C::flux_var(d, cc)) return e * NFL + cc;
+      return d * NFL + cc;
+    };
+#pragma unroll
+    for (int d = 0; d < XD; ++d) {
+#pragma unroll
+      for (int cc = 0; cc < NFL; ++cc)
+        if (flux_row(d, cc) == d * NFL + cc) rows[(d * NFL + cc) * S + k] = nu[C::flux_var(d, cc)];
+#pragma unroll
+      for (int cc = 0; cc < NGR; ++cc) rows[(XD * NFL + d * NGR + cc) * S + k] = lG[d][C::grad_var(cc)];
+    }
+    if constexpr (FW)
+#pragma unroll
+      for (int cc = 0; cc < NGR; ++cc) rows[(XD * (NFL + NGR) + cc) * S + k] = fw[cc];
+    sync();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) mu[v] = 0.0;
+    PDE::source_T(a.pde, nu, mu);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const int dx = d < XD ? d : LX;
+      double lF[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        lF[v] = 0.0;
+        gq[d][v] = 0.0;
+      }
+#pragma unroll
+      for (int cc = 0; cc < NFL; ++cc) {
+        const double x = nu[C::flux_var(d, cc)];
+        lF[C::flux_var(d, cc)] = -(d < XD ? deriv(ln, rows + flux_row(dx, cc) * S, dx, ln.ct[dx], x) : along_z(ln.mzt, x));
+      }
+      PDE::flux_T(d, a.pde, lF, mu);
+#pragma unroll
+      for (int cc = 0; cc < NGR; ++cc) {
+        const int v = C::grad_var(cc);
+        mu[v] += d < XD ? deriv(ln, rows + (XD * NFL + dx * NGR + cc) * S, dx, ln.ct[dx], lG[d][v])
+                        : along_z(ln.mzt, lG[d][v]);
+        if (FW)
+          gq[d][v] = d < XD ? deriv(ln, rows + (XD * (NFL + NGR) + cc) * S, dx, ln.c[dx], fw[cc])
+                            : along_z(ln.mz, fw[cc]);
+      }
+    }
+  }
+
   // mu = L^T nu at this node (FP64; the PDE's transposes): the flux part
   // through D^T of nu's flux components, the non-conservative part through
   // D^T of the gradient adjoints, plus the source's transpose.  With FW, the
@@ -1428,10 +1659,14 @@ struct LinOp {
   // channels of every direction.
   template <bool FW>
   __device__ static __forceinline__ void apply_T(const KArgs& a, double* lds, double* mine,
-                                                 const int (&pk)[DIM], int tid, const double (&nu)[NV],
+                                                 const int (&pk)[DIM], int tid, Lane& ln, const double (&nu)[NV],
                                                  const double* P, const double (&inv_h)[3],
                                                  double (&mu)[NV], const double* fw,
                                                  double (&gq)[DIM][NV]) {
+    if constexpr (LG::on) {
+      apply_T_gather<FW>(a, mine, ln, tid % G::S, nu, P, mu, fw, gq);
+      return;
+    }
     constexpr int NF = FW ? NGR : 0;
     double lB[NV], lG[DIM][NV];
 #pragma unroll
@@ -1619,6 +1854,7 @@ __device__ __forceinline__ void lin_predict_block(const KArgs& a, R* lds, double
   };
 
   R* const mine = lds + lc * GL::CELL_ELEMS;
+  typename Op::Lane ln = Op::lane_data(a, k, tid);
   // Horner's scheme for the time average of the I-th Picard iterate
   R t[NV];
   {
@@ -1635,7 +1871,7 @@ __device__ __forceinline__ void lin_predict_block(const KArgs& a, R* lds, double
       for (int c = 0; c < KG::NGR; ++c) keep[(kk * KG::NGR + c) * S] = double(t[Chan<PDE>::grad_var(c)]);
     }
     R Lt[NV], g[DIM][NV];
-    Op::apply(a, lds, mine, pk, tid, t, P, inv_h, Lt, g);
+    Op::apply(a, lds, mine, pk, tid, ln, t, P, inv_h, Lt, g);
     const R ck = R(a.lin_c[kk]);
 #pragma unroll
     for (int v = 0; v < NV; ++v) t[v] = ck * u[v] + dt * Lt[v];
@@ -1650,7 +1886,7 @@ __device__ __forceinline__ void lin_predict_block(const KArgs& a, R* lds, double
   R vol[NV];
   {
     R g[DIM][NV];
-    Op::apply(a, lds, mine, pk, tid, t, P, inv_h, vol, g);
+    Op::apply(a, lds, mine, pk, tid, ln, t, P, inv_h, vol, g);
     add_sources(0, R(1), vol);
   }
 
@@ -1774,8 +2010,6 @@ __device__ __forceinline__ int corr_cell0(const KArgs& a, int lb) {
 
 // PDEs with a boundary_values function for ADG_BC_USER faces (run-time PDEs
 // that define one)
-template <class... T>
-using kern_void_t = void;
 template <class P, class = void>
 struct HasUserBoundary {
   static constexpr bool value = false;

@@ -143,6 +143,9 @@ struct Elastic3 {
   static constexpr int sym(int i, int d) {
     return i == d ? i : ((i + d == 1) ? 3 : ((i + d == 2) ? 4 : 5));
   }
+  // every nonzero flux component is one of the state's: F[d][v] = Q[flux_of(d, v)]
+  static constexpr bool kFluxCopies = true;
+  static constexpr int flux_of(int d, int v) { return sym(v - 6, d); }
 
   template <class R>
   __device__ static __forceinline__ void fluxes(const R* Q, const R*, const PdeConsts&,
