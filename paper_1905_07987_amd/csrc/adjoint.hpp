@@ -24,23 +24,19 @@
 // A and B of [C][2 dim][NV][F] doubles (face = 2 d + side, side 1 = high):
 //  1. adj_face_project_kernel: A = sum_m l_side(m) / w_m lam(line f, m), the
 //     face projections of lam that the surface integral's transpose needs.
-//  2. adj_rusanov_kernel<true, false>: B = adjoint of each cell's own face
-//     traces (state trace plus folded flux trace) from the fluctuation
-//     adjoints of both cells of the face.
-//  3. adj_predict_lin_kernel: per cell, the linear predictor's Horner sweep
-//     forward from u^n (keeping the iterates' gradient quantities), then the
-//     transposes of the face projection, the volume term and the Horner
+//  2. adj_predict_lin_kernel: per cell, the linear predictor's Horner sweep
+//     forward from u^n (keeping the iterates' gradient quantities); the
+//     adjoint of the cell's own face traces (state trace plus folded flux
+//     trace) from the fluctuation adjoints of both cells of each face; then
+//     the transposes of the face projection, the volume term and the Horner
 //     steps in reverse order; lam <- lam^n, gparams += the cell's volume
-//     terms, B <- face traces of qbar (after B's adjoints have been read).
-//  4. adj_rusanov_kernel<false, true> (PDEs with parameters): gparams += the
-//     Rusanov flux's parameter derivative at every face of the cell.
+//     terms, B <- face traces of qbar.
+//  3. adj_rusanov_kernel (PDEs with parameters): gparams += the Rusanov
+//     flux's parameter derivative at every face of the cell, from A and B.
 // From a kept forward step (KArgs::keep: the Horner quantities and, behind
-// them, the step's face traces of qbar) the sequence is 1; then
-// adj_rusanov_kernel<true, true>, which writes B and each cell's face terms
-// of the parameter gradient (gface, C x nparam doubles behind A and B) in
-// one pass, the qbar traces being the kept ones; then 3 without the forward
-// sweep and without B's qbar traces, adding gface after the cell's volume
-// terms (the state path's order of the two sums).
+// them, the step's face traces of qbar) the sequence is 1, 2: without the
+// forward sweep and without B, the faces' parameter derivative taken with
+// their adjoint (on the kept traces) and added to the cell's volume terms.
 #pragma once
 
 namespace adg {
@@ -116,11 +112,11 @@ adj_face_project_kernel(const KArgs a, const double* __restrict__ lam, double* _
 }
 
 // ---------------------------------------------------------------------------
-// 2./4. Rusanov flux in reverse.  OUT: B <- adjoint of the cell's own face
-// traces.  GRAD: the flux's parameter derivative, the face traces of qbar
-// read from tq (face stride tq_face doubles: NV F for B, 2 NV F for the
-// forward trace array), added to gp (GRAD only) or written to gp (OUT and
-// GRAD: the per-cell face terms that the predictor adjoint adds).
+// Rusanov flux in reverse at face node f of a cell's face, the neighbour
+// periodic.  OUT: out = the adjoint of the cell's own face trace.  GRAD:
+// gp += the flux's parameter derivative, the face traces of qbar read from
+// tq (face stride tq_face doubles: NV F for B, 2 NV F for the forward trace
+// array).
 //
 // Forward, at the face with normal e_d between L (low) and R (high):
 //   s = max(lambda*(pL), lambda*(pR)), G = (FL + FR)/2 - s (qR - qL)/2,
@@ -129,140 +125,139 @@ adj_face_project_kernel(const KArgs a, const double* __restrict__ lam, double* _
 //   face), each scaled by dt / h_d in the update u -= l flL / w ...
 // ---------------------------------------------------------------------------
 template <class PDE, int N, bool OUT, bool GRAD>
+__device__ __forceinline__ void adj_face(const KArgs& a, const double* __restrict__ params, double dt,
+                                         const double* __restrict__ A, const double* __restrict__ tq, int tq_face,
+                                         long long c, int face, int f, double* out, double* gp) {
+  using G = Geo<PDE, N>;
+  constexpr int F = G::F, NV = G::NV, NP = G::NP, DIM = G::DIM;
+  constexpr int NPX = NP > 0 ? NP : 1;
+  const int C0 = a.cells[0], C1 = a.cells[1];
+  const int d = face >> 1, side = face & 1;
+  long long cc[3];
+  cc[0] = c % C0;
+  cc[1] = (c / C0) % C1;
+  cc[2] = DIM == 3 ? c / ((long long)C0 * C1) : 0;
+  cc[d] += side ? 1 : -1;
+  if (cc[d] < 0) cc[d] += a.cells[d];
+  if (cc[d] >= a.cells[d]) cc[d] -= a.cells[d];
+  const long long nb = cc[0] + C0 * (cc[1] + (long long)C1 * cc[2]);
+  const long long cL = side ? c : nb, cR = side ? nb : c;
+  const double scale = -dt * a.inv_h[d];
+  const double* aL = A + ((cL * (2 * DIM) + 2 * d + 1) * NV) * F + f;
+  const double* aR = A + ((cR * (2 * DIM) + 2 * d + 0) * NV) * F + f;
+  double lL[NV], lR[NV], lG[NV], lBm[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    lL[v] = scale * aL[v * F];
+    lR[v] = scale * aR[v * F];
+    lG[v] = lL[v] - lR[v];
+    lBm[v] = 0.5 * (lL[v] + lR[v]);
+  }
+  double pL[NPX] = {}, pR[NPX] = {}, pm[NPX] = {}, qz[NV];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    pL[p] = params[cL * NP + p];
+    pR[p] = params[cR * NP + p];
+    pm[p] = 0.5 * (pL[p] + pR[p]);
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) qz[v] = 0.0;
+  const double sL = PDE::max_eigen(qz, pL, a.pde, d), sR = PDE::max_eigen(qz, pR, a.pde, d);
+  if constexpr (OUT) {
+    const double s = fmax(sL, sR);
+    double ld[NV], lF[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      ld[v] = -0.5 * s * lG[v];
+      lF[v] = side ? (-lL[v] + 0.5 * lG[v]) : (lR[v] + 0.5 * lG[v]);
+    }
+    if constexpr (PDE::kHasNcp) {
+      double lg[DIM][NV];
+#pragma unroll
+      for (int e = 0; e < DIM; ++e)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) lg[e][v] = 0.0;
+      PDE::ncp_T(pm, a.pde, lBm, lg);
+#pragma unroll
+      for (int e = 0; e < DIM; ++e)
+        if (e == d) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) ld[v] += lg[e][v];
+        }
+    }
+    // qR enters with +ld, qL with -ld
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v] = side ? -ld[v] : ld[v];
+    PDE::flux_T(d, a.pde, lF, out);
+  }
+  if constexpr (GRAD) {
+    const double* tL = tq + (cL * (2 * DIM) + 2 * d + 1) * tq_face + f;
+    const double* tR = tq + (cR * (2 * DIM) + 2 * d + 0) * tq_face + f;
+    double jump[NV], ls = 0.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      jump[v] = tR[v * F] - tL[v * F];
+      ls += -0.5 * jump[v] * lG[v];
+    }
+    const double mine = side ? sL : sR, other = side ? sR : sL;
+    const double share = mine > other ? 1.0 : (mine == other ? 0.5 : 0.0);
+    PDE::max_eigen_dparams(side ? pL : pR, d, share * ls, gp);
+    if constexpr (PDE::kHasNcp) {
+      double g[DIM][NV], gpm[NPX];
+#pragma unroll
+      for (int e = 0; e < DIM; ++e)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) g[e][v] = e == d ? jump[v] : 0.0;
+#pragma unroll
+      for (int p = 0; p < NPX; ++p) gpm[p] = 0.0;
+      PDE::ncp_dparams_T(pm, a.pde, g, lBm, gpm);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) gp[p] += 0.5 * gpm[p];
+    }
+  }
+}
+
+// 3. gp_out += the parameter derivative at every face of each cell.
+template <class PDE, int N>
 __global__ void __launch_bounds__(256)
 adj_rusanov_kernel(const KArgs a, const double* __restrict__ params, const double* __restrict__ clock,
                    const double* __restrict__ A, const double* __restrict__ tq, int tq_face,
-                   double* __restrict__ B, double* __restrict__ gp_out) {
+                   double* __restrict__ gp_out) {
   using G = Geo<PDE, N>;
   using GR = GeoAdjR<PDE, N>;
-  constexpr int F = G::F, NV = G::NV, NP = G::NP, DIM = G::DIM;
+  constexpr int F = G::F, NP = G::NP, DIM = G::DIM;
   constexpr int NPX = NP > 0 ? NP : 1;
   constexpr int TPF = GR::TPF, CPB = GR::CPB;
-  __shared__ double contrib[GRAD ? CPB * TPF * NPX : 1];
+  __shared__ double contrib[CPB * TPF * NPX];
   const int tid = threadIdx.x;
   const long long cell0 = (long long)xcd_block(blockIdx.x, a.nblocks) * CPB;
   const double dt = clock[1];
-  const int C0 = a.cells[0], C1 = a.cells[1];
 
   for (int task = tid; task < CPB * TPF; task += GR::BLOCK) {
-    const int f = task % F;
-    const int face = (task / F) % (2 * DIM);
-    const int c2 = task / TPF;
-    const long long c = cell0 + c2;
+    const long long c = cell0 + task / TPF;
     double gp[NPX];
 #pragma unroll
     for (int p = 0; p < NPX; ++p) gp[p] = 0.0;
-    if (c < a.ncells) {
-      const int d = face >> 1, side = face & 1;
-      long long cc[3];
-      cc[0] = c % C0;
-      cc[1] = (c / C0) % C1;
-      cc[2] = DIM == 3 ? c / ((long long)C0 * C1) : 0;
-      cc[d] += side ? 1 : -1;
-      if (cc[d] < 0) cc[d] += a.cells[d];
-      if (cc[d] >= a.cells[d]) cc[d] -= a.cells[d];
-      const long long nb = cc[0] + C0 * (cc[1] + (long long)C1 * cc[2]);
-      const long long cL = side ? c : nb, cR = side ? nb : c;
-      const double scale = -dt * a.inv_h[d];
-      const double* aL = A + ((cL * (2 * DIM) + 2 * d + 1) * NV) * F + f;
-      const double* aR = A + ((cR * (2 * DIM) + 2 * d + 0) * NV) * F + f;
-      double lL[NV], lR[NV], lG[NV], lBm[NV];
+    if (c < a.ncells)
+      adj_face<PDE, N, false, true>(a, params, dt, A, tq, tq_face, c, (task / F) % (2 * DIM), task % F, nullptr, gp);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        lL[v] = scale * aL[v * F];
-        lR[v] = scale * aR[v * F];
-        lG[v] = lL[v] - lR[v];
-        lBm[v] = 0.5 * (lL[v] + lR[v]);
-      }
-      double pL[NPX] = {}, pR[NPX] = {}, pm[NPX] = {}, qz[NV];
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        pL[p] = params[cL * NP + p];
-        pR[p] = params[cR * NP + p];
-        pm[p] = 0.5 * (pL[p] + pR[p]);
-      }
-#pragma unroll
-      for (int v = 0; v < NV; ++v) qz[v] = 0.0;
-      const double sL = PDE::max_eigen(qz, pL, a.pde, d), sR = PDE::max_eigen(qz, pR, a.pde, d);
-      if constexpr (OUT) {
-        const double s = fmax(sL, sR);
-        double ld[NV], lF[NV], out[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          ld[v] = -0.5 * s * lG[v];
-          lF[v] = side ? (-lL[v] + 0.5 * lG[v]) : (lR[v] + 0.5 * lG[v]);
-        }
-        if constexpr (PDE::kHasNcp) {
-          double lg[DIM][NV];
-#pragma unroll
-          for (int e = 0; e < DIM; ++e)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) lg[e][v] = 0.0;
-          PDE::ncp_T(pm, a.pde, lBm, lg);
-#pragma unroll
-          for (int e = 0; e < DIM; ++e)
-            if (e == d) {
-#pragma unroll
-              for (int v = 0; v < NV; ++v) ld[v] += lg[e][v];
-            }
-        }
-        // qR enters with +ld, qL with -ld
-#pragma unroll
-        for (int v = 0; v < NV; ++v) out[v] = side ? -ld[v] : ld[v];
-        PDE::flux_T(d, a.pde, lF, out);
-        double* o = B + ((c * (2 * DIM) + face) * NV) * F + f;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) o[v * F] = out[v];
-      }
-      if constexpr (GRAD) {
-        const double* tL = tq + (cL * (2 * DIM) + 2 * d + 1) * tq_face + f;
-        const double* tR = tq + (cR * (2 * DIM) + 2 * d + 0) * tq_face + f;
-        double jump[NV], ls = 0.0;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          jump[v] = tR[v * F] - tL[v * F];
-          ls += -0.5 * jump[v] * lG[v];
-        }
-        const double mine = side ? sL : sR, other = side ? sR : sL;
-        const double share = mine > other ? 1.0 : (mine == other ? 0.5 : 0.0);
-        PDE::max_eigen_dparams(side ? pL : pR, d, share * ls, gp);
-        if constexpr (PDE::kHasNcp) {
-          double g[DIM][NV], gpm[NPX];
-#pragma unroll
-          for (int e = 0; e < DIM; ++e)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) g[e][v] = e == d ? jump[v] : 0.0;
-#pragma unroll
-          for (int p = 0; p < NPX; ++p) gpm[p] = 0.0;
-          PDE::ncp_dparams_T(pm, a.pde, g, lBm, gpm);
-#pragma unroll
-          for (int p = 0; p < NP; ++p) gp[p] += 0.5 * gpm[p];
-        }
-      }
-    }
-    if constexpr (GRAD) {
-#pragma unroll
-      for (int p = 0; p < NPX; ++p) contrib[task * NPX + p] = gp[p];
-    }
+    for (int p = 0; p < NPX; ++p) contrib[task * NPX + p] = gp[p];
   }
-  if constexpr (GRAD) {
-    __syncthreads();
-    // fixed-order sum per (cell, parameter): deterministic
-    if (tid < CPB * NP) {
-      const int c2 = tid / NP, p = tid - c2 * NP;
-      const long long c = cell0 + c2;
-      if (c < a.ncells) {
-        double s = 0.0;
-        for (int i = 0; i < TPF; ++i) s += contrib[(c2 * TPF + i) * NPX + p];
-        if constexpr (OUT) gp_out[c * NP + p] = s;
-        else gp_out[c * NP + p] += s;
-      }
+  __syncthreads();
+  // fixed-order sum per (cell, parameter): deterministic
+  if (tid < CPB * NP) {
+    const int c2 = tid / NP, p = tid - c2 * NP;
+    const long long c = cell0 + c2;
+    if (c < a.ncells) {
+      double s = 0.0;
+      for (int i = 0; i < TPF; ++i) s += contrib[(c2 * TPF + i) * NPX + p];
+      gp_out[c * NP + p] += s;
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// 3. Predictor adjoint in the polynomial form of the linear predictor: the
+// 2. Predictor adjoint in the polynomial form of the linear predictor: the
 // forward step's time average is t_0 of Horner's scheme
 //   t_I = c_I u;  t_k = c_k u + dt e_{k+1} w + dt L(m) t_{k+1},
 // and the volume term dt (L qbar + e_0 w).  Its transpose runs the same
@@ -276,6 +271,12 @@ adj_rusanov_kernel(const KArgs a, const double* __restrict__ params, const doubl
 // terms read (those of the non-conservative product); each L^T application
 // differentiates them in the same LDS round.  One thread per node; the
 // adjoint's Picard count is at most n, so the sweeps unroll.
+//
+// hat, the adjoint of the cell's face traces, is worked out here (adj_face,
+// one task per face node) into the cell's LDS: as a kernel of its own it is
+// written and read back, one and a half times a cell's state each way
+// (elastic N = 3, 32^3 cells: 317 us, against 156 + 228 us for the two
+// kernels; 324 us with the cells in order instead of corrector bricks).
 // ---------------------------------------------------------------------------
 template <class PDE, int N>
 struct GeoAdjL {
@@ -285,7 +286,10 @@ struct GeoAdjL {
   using LG = LinGather<PDE, N, double>;
   static constexpr int ROW_ELEMS = LG::on ? LG::SETS * LG::ROWS_T * G::S
                                           : (C::NCH + G::DIM * C::ngrad()) * LinLayout<G>::SP;
-  static constexpr int CELL_ELEMS = cmax(cmax(ROW_ELEMS, G::NV * G::S),
+  // hat and the face nodes' parameter terms
+  static constexpr int HAT = 2 * G::DIM * G::NV * G::F;
+  static constexpr int HAT_ELEMS = HAT + 2 * G::DIM * G::F * G::NP;
+  static constexpr int CELL_ELEMS = cmax(cmax(cmax(ROW_ELEMS, HAT_ELEMS), G::NV * G::S),
                                          G::S * (G::NP > 0 ? G::NP : 1));
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
   static constexpr int by_lds = cmax(1, (76 * 1024) / (CELL_ELEMS * 8));
@@ -300,8 +304,10 @@ template <class PDE, int N>
 __global__ void __launch_bounds__((GeoAdjL<PDE, N>::BLOCK), (GeoAdjL<PDE, N>::MIN_WAVES))
 adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double* __restrict__ params,
                        const double* __restrict__ clock, double* __restrict__ lam,
-                       double* __restrict__ gparams, double* __restrict__ hat,
-                       const double* __restrict__ gface) {
+                       double* __restrict__ gparams, const double* __restrict__ A,
+                       const double* __restrict__ tq, double* __restrict__ B) {
+  // tq: the kept step's face traces (null without a kept step); B: where the
+  // face traces of qbar go (without a kept step)
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
   using GA = GeoAdjL<PDE, N>;
@@ -325,7 +331,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
     ln[d] = G::line_of(d, kk3[0], kk3[1], DIM == 3 ? kk3[2] : 0);
     pk[d] = LinLayout<G>::addr(d, ln[d], kk3[d]);
   }
-  const long long cell0 = (long long)xcd_block(blockIdx.x, a.nblocks) * CPB;
+  const long long cell0 = corr_cell0<DIM, CPB>(a, xcd_block(blockIdx.x, a.nblocks));
   const long long cell = cell0 + lc;
   const bool active = cell < a.ncells;
   const long long cl = active ? cell : a.ncells - 1;  // clamp loads of the ragged tail
@@ -401,27 +407,52 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
     }
   }
 
-  // ---- adjoint of the face traces (read hat before it is overwritten) ----
-  double tseed[NV];
+  // ---- adjoint of the face traces ----
+  double tseed[NV], gp[NPX];
 #pragma unroll
   for (int v = 0; v < NV; ++v) tseed[v] = 0.0;
+#pragma unroll
+  for (int p = 0; p < NPX; ++p) gp[p] = 0.0;
+  Op::sync();  // the forward sweep's last read-backs are done
+  Op::template cell_tasks<2 * DIM * F>(tid, [&](int c2, int it) {
+    const int f = it % F, face = it / F;
+    const long long tcell = cell0 + c2 < a.ncells ? cell0 + c2 : a.ncells - 1;
+    double out[NV], g[NPX];
+    double* const hat = lds + c2 * GA::CELL_ELEMS;
+    if (NP > 0 && keep) {
+#pragma unroll
+      for (int p = 0; p < NPX; ++p) g[p] = 0.0;
+      adj_face<PDE, N, true, true>(a, params, dt, A, tq, 2 * NV * F, tcell, face, f, out, g);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) hat[GA::HAT + it * NP + p] = g[p];
+    } else {
+      adj_face<PDE, N, true, false>(a, params, dt, A, nullptr, 0, tcell, face, f, out, nullptr);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) hat[(face * NV + v) * F + f] = out[v];
+  });
+  Op::sync();
 #pragma unroll
   for (int d = 0; d < DIM; ++d)
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
       const double l = ct_pick<n>(kk3[d], [&](int i) { return side ? T::l1(i) : T::l0(i); });
-      const double* h = hat + ((cl * (2 * DIM) + 2 * d + side) * NV) * F + ln[d];
+      const double* h = mine + (2 * d + side) * NV * F + ln[d];
 #pragma unroll
       for (int v = 0; v < NV; ++v) tseed[v] += l * h[v * F];
     }
+  if (NP > 0 && keep)
+    for (int i = k; i < 2 * DIM * F; i += S)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) gp[p] += mine[GA::HAT + i * NP + p];
+  Op::sync();  // hat is read; the rows are free
 
-  // ---- face traces of qbar = t into hat (for the Rusanov parameter
+  // ---- face traces of qbar = t into B (for the Rusanov parameter
   // derivative; a kept step's are the forward step's own) ----
   if (NP > 0 && !keep) {
-    Op::sync();  // the forward sweep's last read-backs are done
 #pragma unroll
     for (int v = 0; v < NV; ++v) mine[v * S + k] = t[v];
-    Op::sync();  // also: every read of hat above is done
+    Op::sync();
     Op::template cell_tasks<DIM * NV * F>(tid, [&](int c2, int it) {
       const int f = it % F, v = (it / F) % NV, d = it / (F * NV);
       const long long tcell = cell0 + c2;
@@ -429,7 +460,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
       const int st = face_line_node<DIM, n>(d, 0, 1) - face_line_node<DIM, n>(d, 0, 0);
       double e0, e1;
       line_ends<double, n>(lds + c2 * GA::CELL_ELEMS + v * S + face_line_node<DIM, n>(d, f, 0), st, e0, e1);
-      double* h = hat + tcell * (2 * DIM * NV * F) + v * F + f;
+      double* h = B + tcell * (2 * DIM * NV * F) + v * F + f;
       h[(2 * d) * NV * F] = e0;
       h[(2 * d + 1) * NV * F] = e1;
     });
@@ -437,9 +468,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
   }
 
   // ---- volume term: mu_0 = dt L^T lam + E^T hat; parameter term at qbar ----
-  double nu[NV], mu[NV], gp[NPX], lu[NV];
-#pragma unroll
-  for (int p = 0; p < NPX; ++p) gp[p] = 0.0;
+  double nu[NV], mu[NV], lu[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     nu[v] = dt * lam[(cl * NV + v) * S + k];
@@ -489,9 +518,7 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
     if (k < NP && active) {
       double s = 0.0;
       for (int i = 0; i < S; ++i) s += mine[i * NP + k];
-      double g = gparams[cell * NP + k] + s;
-      if (gface) g += gface[cell * NP + k];  // the face terms after the volume terms
-      gparams[cell * NP + k] = g;
+      gparams[cell * NP + k] += s;
     }
   }
 }
@@ -510,39 +537,24 @@ struct AdjLaunch {
     double* B = work + a0.ncells * face_elems;
     // kept step: its face traces of qbar follow the keep buffer's node slots
     const bool kept = a0.keep != nullptr;
-    const double* tq = kept ? a0.keep + a0.ncells * (long long)(KeepGeo<PDE, N>::SLOTS * G::S) : B;
-    double* gface = kept && NP > 0 ? work + 2 * a0.ncells * face_elems : nullptr;
-    KArgs a = a0;
+    const double* tq = kept ? a0.keep + a0.ncells * (long long)(KeepGeo<PDE, N>::SLOTS * G::S) : nullptr;
     using GPj = GeoAdjP<PDE, N>;
     hipLaunchKernelGGL((adj_face_project_kernel<PDE, N>), dim3((unsigned)((a0.ncells + GPj::CPB - 1) / GPj::CPB)),
-                       dim3(GPj::BLOCK), 0, st, a, lam, A);
+                       dim3(GPj::BLOCK), 0, st, a0, lam, A);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.nblocks = (int)((a0.ncells + GR::CPB - 1) / GR::CPB);
-    bool fused = false;
-    if constexpr (NP > 0) {
-      if (kept) {
-        hipLaunchKernelGGL((adj_rusanov_kernel<PDE, N, true, true>), dim3(a.nblocks), dim3(GR::BLOCK), 0, st,
-                           a, params, clock, A, tq, (int)(2 * G::NV * G::F), B, gface);
-        fused = true;
-      }
-    }
-    if (!fused)
-      hipLaunchKernelGGL((adj_rusanov_kernel<PDE, N, true, false>), dim3(a.nblocks), dim3(GR::BLOCK), 0, st,
-                         a, params, clock, A, nullptr, 0, B, nullptr);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    KArgs ap = a0;
+    KArgs a = a0;
     using GL = GeoAdjL<PDE, N>;
-    ap.nblocks = (int)((a0.ncells + GL::CPB - 1) / GL::CPB);
-    hipLaunchKernelGGL((adj_predict_lin_kernel<PDE, N>), dim3(ap.nblocks), dim3(GL::BLOCK), 0, st, ap, Q,
-                       params, clock, lam, gparams, B, gface);
+    a.nblocks = (int)((a0.ncells + GL::CPB - 1) / GL::CPB);
+    hipLaunchKernelGGL((adj_predict_lin_kernel<PDE, N>), dim3(a.nblocks), dim3(GL::BLOCK), 0, st, a, Q, params,
+                       clock, lam, gparams, A, tq, B);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if constexpr (NP > 0) {
       if (!kept) {
-        hipLaunchKernelGGL((adj_rusanov_kernel<PDE, N, false, true>), dim3(a.nblocks), dim3(GR::BLOCK), 0, st,
-                           a, params, clock, A, tq, (int)(G::NV * G::F), nullptr, gparams);
+        a.nblocks = (int)((a0.ncells + GR::CPB - 1) / GR::CPB);
+        hipLaunchKernelGGL((adj_rusanov_kernel<PDE, N>), dim3(a.nblocks), dim3(GR::BLOCK), 0, st, a, params, clock,
+                           A, B, (int)(G::NV * G::F), gparams);
         e = hipGetLastError();
       }
     }

@@ -1282,7 +1282,7 @@ struct FluxCopies<P, kern_void_t<decltype(P::kFluxCopies)>> {
 // and v_mfma_f64_4x4x4 contracts along z in place: 8 writes and 36 reads.
 // Measured, one predictor: N = 2, 45 x 38 x 29 cells 147 -> 91 us (4.3 TB/s);
 // N = 3 with the step's keep buffer, 32^3 cells 171 -> 140 us (6.2 TB/s,
-// mostly writes); its adjoint 317 -> 228 us.  Orders 1 to 3: at N = 4 the
+// mostly writes); the adjoint predictor 317 -> 228 us.  Orders 1 to 3: at N = 4 the
 // gather takes 5 multiplications per derivative against 2.6 of the even-odd
 // line tasks, and 168 registers leave 3 waves per SIMD (a step of 48^3
 // cells 1.48 -> 2.5 ms).
