@@ -2473,19 +2473,28 @@ namespace adg {
 //        blocks of several waves from kPackCells cells on (below, all waves
 //        are on the chip at once and what counts is the time of one: N = 4,
 //        64^2 cells packed 28.5 us, one wave 24.7; 80^2 35.4 against 41.0;
-//        N = 6, 64^2 89.6 against 80.8, 80^2 107 against 132).
-//  pair  a lane pair per node (predict_kernel_pair): everything else.
+//        N = 6, 64^2 89.6 against 80.8, 80^2 107 against 132; N = 5, 3072
+//        cells: a step 44.4 against 46.0, with a source term 49 against 53).
+//  pair  a lane pair per node (predict_kernel_pair): everything else, and 2-D
+//        meshes of less than kPairCells cells, where the time is that of one
+//        wave's chain and a pair shares its time slices (a step of 256
+//        cells: Euler N = 7 36.7 us against 40.6, N = 6 37.7 against 35.1; a
+//        PDE with a source term N = 5 30.4 against 32.4, N = 6 38.7 against
+//        43.5, N = 7 41.9 against 51.7; 2048 cells, N = 7: 84 against 78).
 template <class PDE, int N>
 struct Choose64 {
-  static constexpr long long kLineCells2 = 15000, kPackCells = 5000;
+  static constexpr long long kLineCells2 = 15000, kPackCells = N == 5 ? 3000 : 5000;
+  static constexpr long long kPairCells = PDE::DIM != 2 || N < 5 ? 0 : (PDE::kHasSource ? 1800 : (N == 7 ? 768 : 0));
   static constexpr bool kLine = GeoLine<PDE, N>::fits && !PDE::kLinear;
   static constexpr bool kLineAlways = kLine && PDE::DIM == 3 && !GeoLine<PDE, N>::MF;
   static constexpr bool kN64 = GeoN64<PDE, N>::fits;
   static constexpr bool kCanPack = kN64 && GeoN64<PDE, N>::CAN_PACK;
+  static constexpr bool kCanPair = !kN64 || kPairCells > 0;
   __host__ __device__ static constexpr bool line(long long ncells, int guess, int iters) {
     if (PDE::DIM == 2) return kLine && ncells >= kLineCells2;
     return kLineAlways || (kLine && (guess == ADG_GUESS_CERK || iters >= 3));
   }
+  __host__ __device__ static constexpr bool pair(long long ncells) { return !kN64 || ncells < kPairCells; }
   __host__ __device__ static constexpr bool pack(long long ncells) { return kCanPack && ncells >= kPackCells; }
 };
 
@@ -2593,16 +2602,22 @@ struct Launch {
       launch_line(a, Q, params, clock, Qout, traces, st);
     } else if constexpr (Ch::kLineAlways) {
       return hipErrorNotSupported;  // not reached
-    } else if constexpr (Ch::kN64) {
-      if (Ch::pack(a.ncells))
-        launch_n64<Ch::kCanPack>(a, Q, params, clock, Qout, traces, st);
-      else
-        launch_n64<false>(a, Q, params, clock, Qout, traces, st);
     } else {
-      using GA = GeoA2<PDE, N, double>;
-      a.nblocks = blocks_a<GA>(a);
-      hipLaunchKernelGGL((predict_kernel_pair<PDE, N, double>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
-                         st, a, Q, params, clock, Qout, traces);
+      if constexpr (Ch::kCanPair) {
+        if (Ch::pair(a.ncells)) {
+          using GA = GeoA2<PDE, N, double>;
+          a.nblocks = blocks_a<GA>(a);
+          hipLaunchKernelGGL((predict_kernel_pair<PDE, N, double>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
+                             st, a, Q, params, clock, Qout, traces);
+          return hipGetLastError();
+        }
+      }
+      if constexpr (Ch::kN64) {
+        if (Ch::pack(a.ncells))
+          launch_n64<Ch::kCanPack>(a, Q, params, clock, Qout, traces, st);
+        else
+          launch_n64<false>(a, Q, params, clock, Qout, traces, st);
+      }
     }
     return hipGetLastError();
   }

@@ -75,6 +75,12 @@ def test_step_2d_against_oracle(order, cells, guess, source):
     s.close()
 
 
+@pytest.mark.parametrize("order,cells", [(5, [54, 55]), (5, [55, 56]), (7, [27, 28]), (7, [28, 28])])
+def test_small_mesh_rules_against_oracle(order, cells):
+    # either side of the counts for lane pairs (N = 7) and packed blocks (N = 5)
+    test_step_2d_against_oracle(order, cells, "constant", True)
+
+
 @pytest.mark.parametrize("order", [1, 2, 3])
 def test_nan_stays_in_its_cell(order):
     cells = [4, 3, 3]

@@ -297,3 +297,20 @@ def test_user_euler_point_source_vs_builtin(order):
         s.close()
     assert rel_l2(out[0], out[1]) <= TOL
     assert rel_l2(out[1], Q0) > 1e-6
+
+
+@pytest.mark.parametrize("order,cells", [(5, [41, 43]), (5, [42, 43]), (6, [42, 43]), (7, [41, 43]), (7, [42, 43])])
+def test_user_source_term_on_either_side_of_the_pair_rule(order, cells):
+    """A run-time PDE with a source term that is not declared linear, on 2-D
+    meshes just below and above the cell count up to which lane pairs take
+    its predictor: advection with decay against the oracle."""
+    P = O.problem(2, order, O.ADVECTION, cells, adv=(0.7, -0.4, 0.0), kappa=0.3)
+    s = adg.Solver(2, order, "advection", cells, source=ADVECTION2.replace("LINEAR = true", "LINEAR = false"))
+    Q0 = np.random.default_rng(90 + order).normal(size=(P.ncells, 1, P.S))
+    dt = O.stable_dt(P, Q0)[0]
+    Qo = O.step(P, Q0, None, dt, 0.0)
+    Q, clock = dev(Q0), dev([0.0, dt])
+    s.step(Q, None, clock, next_dt=False)
+    torch.cuda.synchronize()
+    assert rel_l2(Q.cpu().numpy(), Qo) <= TOL
+    s.close()
