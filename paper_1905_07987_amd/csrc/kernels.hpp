@@ -113,7 +113,19 @@ template <class PDE, int N, class R, bool MF = false>
 struct GeoA1 {
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
-  static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;          // per cell, in R
+  // 3-D cells of 6^3 nodes: rows without bank conflicts.  An 8-byte access is
+  // served 32 lanes at a time, two rows in one ds_read2 16 lanes of either;
+  // at a line stride of 7 the rows of all three directions straddled banks
+  // (28 % of the LDS cycles).  Here the node threads' 32 consecutive lanes
+  // take 32 banks in every direction: x and z rows in node order, point m of
+  // y-line l at l + 38 m.  Line tasks of x read pairs of neighbours (lines 6
+  // apart: even and odd banks), those of y and z single elements (consecutive
+  // lines).  40^3 cells 3.45 -> 3.00 ms per predictor.
+  static constexpr bool NODE_ROWS = !MF && G::DIM == 3 && G::n == 6 && sizeof(R) == 4 && C::ngrad() == 0;
+  static constexpr int YS = NODE_ROWS ? 38 : 0;               // between the points of a y-line
+  static constexpr int ROW_X = G::S, ROW_Y = G::n * YS;       // elements of a row (z: as x)
+  static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;       // per cell, in R
+  static_assert(!NODE_ROWS || C::NFLUX * (2 * ROW_X + ROW_Y) <= C::NCH * G::SP, "rows exceed the cell's LDS");
   static constexpr int FIN_ELEMS = (G::NV + C::NFLUX) * G::SP;   // per cell, in R
   static constexpr int CELL_ELEMS = cmax(ITER_ELEMS, FIN_ELEMS);
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
@@ -383,6 +395,16 @@ __device__ __forceinline__ void bf16x3_line_derivs(int NLINES, RowOf row_of, Sca
 // ---------------------------------------------------------------------------
 // Kernel A, one thread per node (used for the FP32 predictor).
 // ---------------------------------------------------------------------------
+// An element of the rows as an 8-byte access of its own (volatile: not paired
+// with another).
+typedef double __attribute__((may_alias)) pair_bits;
+__device__ __forceinline__ Pair<float> pair_get(const Pair<float>* p) {
+  return __builtin_bit_cast(Pair<float>, (double)*(const volatile __attribute__((address_space(3))) pair_bits*)p);
+}
+__device__ __forceinline__ void pair_put(Pair<float>* p, Pair<float> x) {
+  *(volatile __attribute__((address_space(3))) pair_bits*)p = __builtin_bit_cast(double, x);
+}
+
 template <class PDE, int N, class R, bool MF = false>
 __global__ void __launch_bounds__((GeoA1<PDE, N, R, MF>::BLOCK), (GeoA1<PDE, N, R, MF>::MIN_WAVES))
 predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ params,
@@ -408,13 +430,22 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
   // part in the line derivatives
   const bool node = !MF || tid < CPB * S;
   const int lc = node ? tid / S : 0, k = node ? tid - lc * S : 0;
-  int pk[DIM];  // this node's slot in the LDS rows of each direction
+  int pk[DIM], pf[DIM];  // this node's slot in the LDS rows of each direction, and in those of the final phase
   {
     const int kx = k % n, ky = (k / n) % n, kz = DIM == 3 ? k / (n * n) : 0;
     const int kd[3] = {kx, ky, kz};
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) pk[d] = G::line_of(d, kx, ky, kz) * G::LS + kd[d];
+    for (int d = 0; d < DIM; ++d) {
+      pf[d] = G::line_of(d, kx, ky, kz) * G::LS + kd[d];
+      pk[d] = GA::NODE_ROWS ? (d == 1 ? kx + n * kz + GA::YS * ky : k) : pf[d];
+    }
   }
+  // first element of channel c of direction d
+  auto row_of = [](int d, int c) {
+    if (!GA::NODE_ROWS) return (d * NCHD + c) * SP;
+    return d == 0 ? c * GA::ROW_X
+                  : NFL * GA::ROW_X + (d == 1 ? c * GA::ROW_Y : NFL * GA::ROW_Y + c * GA::ROW_X);
+  };
   const long long cell0 = (long long)xcd_block(blockIdx.x, a.nblocks) * CPB;
   const long long cell = cell0 + lc;
   const bool active = node && cell < a.ncells;
@@ -503,13 +534,15 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
 #pragma unroll
               for (int c = 0; c < NFL; ++c) {
                 const int v = C::flux_var(d, c);
-                mine[(d * NCHD + c) * SP + pk[d]] = P2{Fa[d][v], two ? Fb[d][v] : R(0)};
+                const P2 x = P2{Fa[d][v], two ? Fb[d][v] : R(0)};
+                if constexpr (GA::NODE_ROWS) pair_put(&mine[row_of(d, c) + pk[d]], x);
+                else mine[row_of(d, c) + pk[d]] = x;
               }
             }
 #pragma unroll
             for (int c = 0; c < NGR; ++c) {
               const int v = C::grad_var(c);
-              mine[(d * NCHD + NFL + c) * SP + pk[d]] = P2{q[j0][v], two ? q[j1][v] : R(0)};
+              mine[row_of(d, NFL + c) + pk[d]] = P2{q[j0][v], two ? q[j1][v] : R(0)};
             }
           }
         }
@@ -527,6 +560,34 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
                 return lds2 + c2 * (GA::CELL_ELEMS / 2) + (d * NCHD + ch) * SP + l * G::LS;
               },
               [&](int) { return 1.0f; }, BLOCK / 64, Amf);
+        } else if constexpr (GA::NODE_ROWS) {
+          // a direction at a time, one task per (channel, line)
+          static_assert(CPB == 1 && NFL * F <= BLOCK, "one round of tasks per direction");
+          const int ch = tid / F, l = tid - ch * F;
+          if (tid < NFL * F) {
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+              P2* const row = lds2 + row_of(d, 0) + (d == 1 ? ch * GA::ROW_Y + l : ch * GA::ROW_X + (d == 0 ? n * l : l));
+              constexpr int st[3] = {1, GA::YS, F};
+              P2 x[n];
+#pragma unroll
+              for (int m = 0; m < n; ++m) {
+                if (d == 0) x[m] = row[m];
+                else x[m] = pair_get(&row[m * st[d]]);
+              }
+#pragma unroll
+              for (int i = 0; i < n; ++i) {
+                R y0 = R(0), y1 = R(0);
+#pragma unroll
+                for (int m = 0; m < n; ++m) {
+                  y0 += T::D(i, m) * x[m].x;
+                  y1 += T::D(i, m) * x[m].y;
+                }
+                if (d == 0) row[i] = P2{y0, y1};
+                else pair_put(&row[i * st[d]], P2{y0, y1});
+              }
+            }
+          }
         } else
         for (int task = tid; task < CPB * DIM * 2 * F; task += BLOCK) {
           const int l = task % F;
@@ -569,13 +630,15 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
           for (int c = 0; c < NFL; ++c) {
             if constexpr (FIN) break;
             const int v = C::flux_var(d, c);
-            const P2 t = mine[(d * NCHD + c) * SP + pk[d]];
+            P2 t;
+            if constexpr (GA::NODE_ROWS) t = pair_get(&mine[row_of(d, c) + pk[d]]);
+            else t = mine[row_of(d, c) + pk[d]];
             divA[v] = C::first_flux_dir(v) == d ? t.x * ih : fma_r(t.x, ih, divA[v]);
             divB[v] = C::first_flux_dir(v) == d ? t.y * ih : fma_r(t.y, ih, divB[v]);
           }
 #pragma unroll
           for (int c = 0; c < NGR; ++c) {
-            const P2 t = mine[(d * NCHD + NFL + c) * SP + pk[d]];
+            const P2 t = mine[row_of(d, NFL + c) + pk[d]];
             gA[d][C::grad_var(c)] = t.x * ih;
             gB[d][C::grad_var(c)] = t.y * ih;
           }
@@ -693,10 +756,10 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) fin_mine[d * FIN_D + v * SP + pk[d]] = qbar[v];
+      for (int v = 0; v < NV; ++v) fin_mine[d * FIN_D + v * SP + pf[d]] = qbar[v];
 #pragma unroll
       for (int c = 0; c < NFL; ++c)
-        fin_mine[d * FIN_D + (NV + c) * SP + pk[d]] = Fbar[d][C::flux_var(d, c)];
+        fin_mine[d * FIN_D + (NV + c) * SP + pf[d]] = Fbar[d][C::flux_var(d, c)];
     }
   }
   __syncthreads();
@@ -757,7 +820,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
 #pragma unroll
   for (int d = 0; d < DIM; ++d)
 #pragma unroll
-    for (int c = 0; c < NFL; ++c) divF[C::flux_var(d, c)] += fin_mine[d * FIN_D + (NV + c) * SP + pk[d]];
+    for (int c = 0; c < NFL; ++c) divF[C::flux_var(d, c)] += fin_mine[d * FIN_D + (NV + c) * SP + pf[d]];
 
   if (active) {
 #pragma unroll
