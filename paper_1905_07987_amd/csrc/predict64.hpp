@@ -78,7 +78,23 @@ struct GeoN64 {
   // points over distinct banks)
   static constexpr int EI = GPM ? C::NCH * F + 1 : ES, RS = GPM ? F : SP;
   __host__ __device__ static constexpr int islot(int line, int pos) { return GPM ? line + pos * EI : slot(line, pos); }
-  static constexpr int ITER_ELEMS = GPM ? 2 * n * EI : (PAIR ? 2 : 1) * C::NCH * SP;
+  // 3-D n = 5 (single slices): the Picard rounds' rows a direction at a time,
+  // so that the 32 lanes that an 8-byte access is served at a time take 32
+  // banks: x-lines and the nodes of z in node order, z rows 153 apart (the
+  // next channel's lines continue on the next banks), point m of y-line l at
+  // l + 27 m (7 cycles per 4 groups of nodes; no layout of 160 elements has
+  // fewer with conflict-free lines).  Every access is one of its own: a
+  // paired one is served 16 lanes of either row at a time and collides.
+  // (25 % of the LDS cycles were conflicts, now 16 % of fewer; 37 x 26 x 19
+  // cells 0.63 -> 0.57 ms.)
+  static constexpr bool DIRS = DIM == 3 && n == 5 && !PAIR && C::ngrad() == 0;
+  static constexpr int ZP = 153;  // elements of a y or z row
+  __host__ __device__ static constexpr int drow(int d, int c) {
+    return d == 0 ? c * S : C::NFLUX * (S + (d - 1) * ZP) + c * ZP;
+  }
+  __host__ __device__ static constexpr int dstep(int d) { return d == 0 ? 1 : (d == 1 ? 27 : 25); }
+  static constexpr int ITER_ELEMS =
+      DIRS ? C::NFLUX * (S + 2 * ZP) : (GPM ? 2 * n * EI : (PAIR ? 2 : 1) * C::NCH * SP);
   static constexpr int FIN_ELEMS = (FINDIR ? 1 : DIM) * (NV + C::NFLUX) * SP;
   static constexpr int CELL_ELEMS =
       cmax(ITER_ELEMS, FIN_ELEMS + (FINDIR && CPB == 1 ? NV * BLOCK : 0)) + (PAIR ? 2 : 1) * CELL_PAD;
@@ -117,6 +133,14 @@ template <bool GPM>
 __device__ __forceinline__ int n64_line_perm(int d, int line) {
   if constexpr (GPM) return kN64LinePerm[d][line];
   return line;
+}
+
+// An element of the rows as an access of its own (not paired with another).
+__device__ __forceinline__ double n64_get(const double* p) {
+  return *(const volatile __attribute__((address_space(3))) double*)p;
+}
+__device__ __forceinline__ void n64_put(double* p, double x) {
+  *(volatile __attribute__((address_space(3))) double*)p = x;
 }
 
 // PDEs that provide flux_dir(Q, P, pc, d, F), the flux of one direction
@@ -164,7 +188,8 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
       pk[d] = GN::slot(GN::G::line_of(d, kx, ky, kz), kd[d]);
-      pki[d] = GN::islot(n64_line_perm<GN::GPM>(d, GN::G::line_of(d, kx, ky, kz)), kd[d]);
+      pki[d] = GN::DIRS ? (d == 1 ? kx + n * kz + GN::dstep(1) * ky : kr)
+                        : GN::islot(n64_line_perm<GN::GPM>(d, GN::G::line_of(d, kx, ky, kz)), kd[d]);
     }
   }
 
@@ -250,7 +275,11 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
             for (int v = 0; v < NV; ++v) Fa[v] = Fall[d][v];
           }
 #pragma unroll
-          for (int cc = 0; cc < NFL; ++cc) mine[(d * NCHD + cc) * RS + pki[d]] = Fa[C::flux_var(d, cc)];
+          for (int cc = 0; cc < NFL; ++cc) {
+            const double f = Fa[C::flux_var(d, cc)];
+            if constexpr (GN::DIRS) n64_put(&mine[GN::drow(d, cc) + pki[d]], f);
+            else mine[(d * NCHD + cc) * RS + pki[d]] = f;
+          }
         }
       }
 #pragma unroll
@@ -261,6 +290,23 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
     __syncthreads();
     constexpr int CH0 = FIN ? NFL : 0;
     constexpr int NCT = NCHD - CH0;
+    if constexpr (GN::DIRS) {
+      // one task per (channel, line) of a direction
+      static_assert(CPB == 1 && NFL * F <= BLOCK, "one round of tasks per direction");
+      const int ch = tid / F, l = tid - ch * F;
+      if (tid < NFL * F) {
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+          double* const row = lds + GN::drow(d, 0) + (d == 0 ? ch * S + n * l : ch * GN::ZP + l);
+          double x[n], y[n];
+#pragma unroll
+          for (int m = 0; m < n; ++m) x[m] = n64_get(&row[m * GN::dstep(d)]);
+          line_deriv<double, n>(x, y, 1.0);
+#pragma unroll
+          for (int i = 0; i < n; ++i) n64_put(&row[i * GN::dstep(d)], y[i]);
+        }
+      }
+    } else
     for (int task = tid; task < CPB * DIM * NCT * F; task += BLOCK) {
       const int l = task % F;
       const int ch = CH0 + (task / F) % NCT;
@@ -283,7 +329,9 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
       for (int cc = 0; cc < NFL; ++cc) {
         if constexpr (FIN) break;
         const int v = C::flux_var(d, cc);
-        const double t = rmine[(d * NCHD + cc) * RS + pki[d]];
+        double t;
+        if constexpr (GN::DIRS) t = n64_get(&rmine[GN::drow(d, cc) + pki[d]]);
+        else t = rmine[(d * NCHD + cc) * RS + pki[d]];
         div0[v] = C::first_flux_dir(v) == d ? t * ih : fma_r(t, ih, div0[v]);
       }
 #pragma unroll
