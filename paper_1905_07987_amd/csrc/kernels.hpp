@@ -113,19 +113,27 @@ template <class PDE, int N, class R, bool MF = false>
 struct GeoA1 {
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
-  // 3-D cells of 6^3 nodes: rows without bank conflicts.  An 8-byte access is
-  // served 32 lanes at a time, two rows in one ds_read2 16 lanes of either;
-  // at a line stride of 7 the rows of all three directions straddled banks
-  // (28 % of the LDS cycles).  Here the node threads' 32 consecutive lanes
-  // take 32 banks in every direction: x and z rows in node order, point m of
-  // y-line l at l + 38 m.  Line tasks of x read pairs of neighbours (lines 6
-  // apart: even and odd banks), those of y and z single elements (consecutive
-  // lines).  40^3 cells 3.45 -> 3.00 ms per predictor.
-  static constexpr bool NODE_ROWS = !MF && G::DIM == 3 && G::n == 6 && sizeof(R) == 4 && C::ngrad() == 0;
-  static constexpr int YS = NODE_ROWS ? 38 : 0;               // between the points of a y-line
-  static constexpr int ROW_X = G::S, ROW_Y = G::n * YS;       // elements of a row (z: as x)
+  // 3-D cells of 5^3 and 6^3 nodes: rows without bank conflicts.  An 8-byte
+  // access is served 32 lanes at a time, two rows in one ds_read2 16 lanes of
+  // either; at a line stride of 7 the rows of all three directions straddled
+  // banks (n = 6: 28 % of the LDS cycles).  Here the node threads' 32
+  // consecutive lanes take 32 banks in nearly every access: x and z rows in
+  // node order, point m of y-line l at l + YS m.  Line tasks of x at n = 6
+  // read pairs of neighbours (lines 6 apart: even and odd banks), all others
+  // single elements (consecutive lines, or lines 5 apart).  A predictor, N =
+  // 5, 40^3 cells 3.45 -> 3.00 ms.
+  static constexpr bool NODE_ROWS =
+      !MF && G::DIM == 3 && (G::n == 5 || G::n == 6) && sizeof(R) == 4 && C::ngrad() == 0;
+  static constexpr int YS = G::n == 5 ? 27 : 38;               // between the points of a y-line
+  // elements of a row of each direction (n = 5: the next channel's lines of
+  // y and z continue on the next banks)
+  static constexpr int ROW_X = G::S, ROW_Y = G::n == 5 ? 153 : 228, ROW_Z = G::n == 5 ? 153 : G::S;
+  // Elsewhere the rows' accesses are single ones where that was faster: 2-D
+  // (N = 2 .. 7, a step of 6e6 nodes 5 to 9 % less) and 3-D N <= 2 (4 %);
+  // 3-D N = 3 pairs them (1 % the other way).
+  static constexpr bool ALONE = G::DIM == 2 || G::n <= 3 || NODE_ROWS;
   static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;       // per cell, in R
-  static_assert(!NODE_ROWS || C::NFLUX * (2 * ROW_X + ROW_Y) <= C::NCH * G::SP, "rows exceed the cell's LDS");
+  static_assert(!NODE_ROWS || C::NFLUX * (ROW_X + ROW_Y + ROW_Z) <= C::NCH * G::SP, "rows exceed the cell's LDS");
   static constexpr int FIN_ELEMS = (G::NV + C::NFLUX) * G::SP;   // per cell, in R
   static constexpr int CELL_ELEMS = cmax(ITER_ELEMS, FIN_ELEMS);
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
@@ -395,14 +403,19 @@ __device__ __forceinline__ void bf16x3_line_derivs(int NLINES, RowOf row_of, Sca
 // ---------------------------------------------------------------------------
 // Kernel A, one thread per node (used for the FP32 predictor).
 // ---------------------------------------------------------------------------
-// An element of the rows as an 8-byte access of its own (volatile: not paired
-// with another).
+// An element of the rows; ALONE: as an 8-byte access of its own (volatile: not
+// paired with another).
 typedef double __attribute__((may_alias)) pair_bits;
+template <bool ALONE>
 __device__ __forceinline__ Pair<float> pair_get(const Pair<float>* p) {
-  return __builtin_bit_cast(Pair<float>, (double)*(const volatile __attribute__((address_space(3))) pair_bits*)p);
+  if constexpr (ALONE)
+    return __builtin_bit_cast(Pair<float>, (double)*(const volatile __attribute__((address_space(3))) pair_bits*)p);
+  return *p;
 }
+template <bool ALONE>
 __device__ __forceinline__ void pair_put(Pair<float>* p, Pair<float> x) {
-  *(volatile __attribute__((address_space(3))) pair_bits*)p = __builtin_bit_cast(double, x);
+  if constexpr (ALONE) *(volatile __attribute__((address_space(3))) pair_bits*)p = __builtin_bit_cast(double, x);
+  else *p = x;
 }
 
 template <class PDE, int N, class R, bool MF = false>
@@ -444,7 +457,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
   auto row_of = [](int d, int c) {
     if (!GA::NODE_ROWS) return (d * NCHD + c) * SP;
     return d == 0 ? c * GA::ROW_X
-                  : NFL * GA::ROW_X + (d == 1 ? c * GA::ROW_Y : NFL * GA::ROW_Y + c * GA::ROW_X);
+                  : NFL * GA::ROW_X + (d == 1 ? c * GA::ROW_Y : NFL * GA::ROW_Y + c * GA::ROW_Z);
   };
   const long long cell0 = (long long)xcd_block(blockIdx.x, a.nblocks) * CPB;
   const long long cell = cell0 + lc;
@@ -535,8 +548,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
               for (int c = 0; c < NFL; ++c) {
                 const int v = C::flux_var(d, c);
                 const P2 x = P2{Fa[d][v], two ? Fb[d][v] : R(0)};
-                if constexpr (GA::NODE_ROWS) pair_put(&mine[row_of(d, c) + pk[d]], x);
-                else mine[row_of(d, c) + pk[d]] = x;
+                pair_put<GA::ALONE>(&mine[row_of(d, c) + pk[d]], x);
               }
             }
 #pragma unroll
@@ -561,19 +573,21 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
               },
               [&](int) { return 1.0f; }, BLOCK / 64, Amf);
         } else if constexpr (GA::NODE_ROWS) {
-          // a direction at a time, one task per (channel, line)
-          static_assert(CPB == 1 && NFL * F <= BLOCK, "one round of tasks per direction");
-          const int ch = tid / F, l = tid - ch * F;
-          if (tid < NFL * F) {
+          // a direction at a time, one task per (cell, channel, line)
+          constexpr int NT = NFL * F;
+          static_assert(CPB * NT <= BLOCK, "one round of tasks per direction");
+          const int c2 = tid / NT, ch = (tid / F) % NFL, l = tid % F;
+          if (tid < CPB * NT) {
 #pragma unroll
             for (int d = 0; d < DIM; ++d) {
-              P2* const row = lds2 + row_of(d, 0) + (d == 1 ? ch * GA::ROW_Y + l : ch * GA::ROW_X + (d == 0 ? n * l : l));
-              constexpr int st[3] = {1, GA::YS, F};
+              constexpr int st[3] = {1, GA::YS, F}, rs[3] = {GA::ROW_X, GA::ROW_Y, GA::ROW_Z};
+              constexpr bool pairs = n == 6;  // (x)
+              P2* const row = lds2 + c2 * (GA::CELL_ELEMS / 2) + row_of(d, 0) + ch * rs[d] + (d == 0 ? n * l : l);
               P2 x[n];
 #pragma unroll
               for (int m = 0; m < n; ++m) {
-                if (d == 0) x[m] = row[m];
-                else x[m] = pair_get(&row[m * st[d]]);
+                if (d == 0) x[m] = pair_get<!pairs>(&row[m]);
+                else x[m] = pair_get<true>(&row[m * st[d]]);
               }
 #pragma unroll
               for (int i = 0; i < n; ++i) {
@@ -583,8 +597,8 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
                   y0 += T::D(i, m) * x[m].x;
                   y1 += T::D(i, m) * x[m].y;
                 }
-                if (d == 0) row[i] = P2{y0, y1};
-                else pair_put(&row[i * st[d]], P2{y0, y1});
+                if (d == 0) pair_put<!pairs>(&row[i], P2{y0, y1});
+                else pair_put<true>(&row[i * st[d]], P2{y0, y1});
               }
             }
           }
@@ -599,7 +613,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
           for (int c = cb; c < ce; ++c) {
             P2 x[n];
 #pragma unroll
-            for (int m = 0; m < n; ++m) x[m] = row[c * SP + m];
+            for (int m = 0; m < n; ++m) x[m] = pair_get<GA::ALONE>(&row[c * SP + m]);
 #pragma unroll
             for (int i = 0; i < n; ++i) {
               R y0 = R(0), y1 = R(0);
@@ -608,7 +622,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
                 y0 += T::D(i, m) * x[m].x;
                 y1 += T::D(i, m) * x[m].y;
               }
-              row[c * SP + i] = P2{y0, y1};
+              pair_put<GA::ALONE>(&row[c * SP + i], P2{y0, y1});
             }
           }
         }
@@ -630,9 +644,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
           for (int c = 0; c < NFL; ++c) {
             if constexpr (FIN) break;
             const int v = C::flux_var(d, c);
-            P2 t;
-            if constexpr (GA::NODE_ROWS) t = pair_get(&mine[row_of(d, c) + pk[d]]);
-            else t = mine[row_of(d, c) + pk[d]];
+            const P2 t = pair_get<GA::ALONE>(&mine[row_of(d, c) + pk[d]]);
             divA[v] = C::first_flux_dir(v) == d ? t.x * ih : fma_r(t.x, ih, divA[v]);
             divB[v] = C::first_flux_dir(v) == d ? t.y * ih : fma_r(t.y, ih, divB[v]);
           }
@@ -1400,6 +1412,18 @@ struct GeoL {
   static constexpr int MIN_WAVES = 3;
 };
 
+// An element of the rows; ALONE: as an access of its own.
+template <bool ALONE, class R>
+__device__ __forceinline__ R row_get(const R* p) {
+  if constexpr (ALONE) return *(const volatile __attribute__((address_space(3))) R*)p;
+  return *p;
+}
+template <bool ALONE, class R>
+__device__ __forceinline__ void row_put(R* p, R x) {
+  if constexpr (ALONE) *(volatile __attribute__((address_space(3))) R*)p = x;
+  else *p = x;
+}
+
 // node index of position m on line l of direction d
 template <class G>
 __device__ __forceinline__ int line_node(int d, int l, int m) {
@@ -1546,18 +1570,18 @@ struct LinOp {
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
 #pragma unroll
-      for (int cc = 0; cc < NFL; ++cc) mine[(d * NCHD + cc) * SP + pk[d]] = Fl[d][C::flux_var(d, cc)];
+      for (int cc = 0; cc < NFL; ++cc) row_put<LL::k5>(&mine[(d * NCHD + cc) * SP + pk[d]], Fl[d][C::flux_var(d, cc)]);
 #pragma unroll
-      for (int cc = 0; cc < NGR; ++cc) mine[(d * NCHD + NFL + cc) * SP + pk[d]] = t[C::grad_var(cc)];
+      for (int cc = 0; cc < NGR; ++cc) row_put<LL::k5>(&mine[(d * NCHD + NFL + cc) * SP + pk[d]], t[C::grad_var(cc)]);
     }
     sync();
     auto line = [&](R* row) {
       R x[n], y[n];
 #pragma unroll
-      for (int m = 0; m < n; ++m) x[m] = row[m];
+      for (int m = 0; m < n; ++m) x[m] = row_get<LL::k5>(&row[m]);
       line_deriv<R, n>(x, y, R(1));
 #pragma unroll
-      for (int i = 0; i < n; ++i) row[i] = y[i];
+      for (int i = 0; i < n; ++i) row_put<LL::k5>(&row[i], y[i]);
     };
     if constexpr (CELL_ELEMS == NCH * SP) {
       // the lines of every cell, channel and direction follow one another at
@@ -1587,11 +1611,11 @@ struct LinOp {
 #pragma unroll
       for (int cc = 0; cc < NFL; ++cc) {
         const int v = C::flux_var(d, cc);
-        const R x = mine[(d * NCHD + cc) * SP + pk[d]];
+        const R x = row_get<LL::k5>(&mine[(d * NCHD + cc) * SP + pk[d]]);
         divF[v] = C::first_flux_dir(v) == d ? x * ih : fma_r(x, ih, divF[v]);
       }
 #pragma unroll
-      for (int cc = 0; cc < NGR; ++cc) g[d][C::grad_var(cc)] = mine[(d * NCHD + NFL + cc) * SP + pk[d]] * ih;
+      for (int cc = 0; cc < NGR; ++cc) g[d][C::grad_var(cc)] = row_get<LL::k5>(&mine[(d * NCHD + NFL + cc) * SP + pk[d]]) * ih;
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v)

@@ -81,6 +81,34 @@ def test_small_mesh_rules_against_oracle(order, cells):
     test_step_2d_against_oracle(order, cells, "constant", True)
 
 
+@pytest.mark.parametrize("cells", [[1, 1, 1], [3, 5, 2]])
+@pytest.mark.parametrize("iters,guess,source", [(0, "constant", True), (1, "constant", False), (0, "cerk", False)])
+def test_five_cubed_rows_against_oracle(cells, iters, guess, source):
+    # 3-D N = 4, whose rows are laid out a direction at a time
+    test_step_against_oracle(4, cells, iters, guess, source)
+
+
+@pytest.mark.parametrize("dim,order,cells", [(2, 1, [5, 7]), (2, 4, [7, 3]), (2, 6, [3, 5]), (2, 7, [3, 3]), (3, 2, [3, 2, 5]),
+                                             (3, 4, [1, 1, 1]), (3, 4, [3, 1, 3]), (3, 5, [1, 2, 1])])
+def test_fp32_rows_against_oracle(dim, order, cells):
+    """The FP32 predictor's LDS rows at ragged cell counts; bar: 1e-5, that of
+    the mixed-precision predictor against the FP64 oracle."""
+    print("[gpu-test] fp32 rows", dim, order, cells, flush=True)
+    P = O.problem(dim, order, O.EULER, cells, cfl=0.4)
+    s = adg.Solver(dim, order, "euler", cells, cfl=0.4, precision="fp32")
+    Q0 = inputs.smooth_euler_state(O.node_coords(P), 29)
+    dt = O.stable_dt(P, Q0)[0]
+    Qo = O.step(P, Q0, None, dt, 0.0)
+    Q, clock = dev(Q0), dev([0.0, dt])
+    s.step(Q, None, clock, next_dt=False)
+    torch.cuda.synchronize()
+    g = Q.cpu().numpy()
+    assert rel_l2(g, Qo) <= 1e-5
+    # every cell's increment, not only the mean: no cell took another's rows
+    assert np.abs(g - Qo).max() <= 1e-4 * np.abs(Qo - Q0).max()
+    s.close()
+
+
 @pytest.mark.parametrize("order", [1, 2, 3])
 def test_nan_stays_in_its_cell(order):
     cells = [4, 3, 3]
