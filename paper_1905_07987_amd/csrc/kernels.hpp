@@ -1766,11 +1766,11 @@ struct LinOp {
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
 #pragma unroll
-      for (int cc = 0; cc < NFL; ++cc) mine[(d * NCHD + cc) * SP + pk[d]] = nu[C::flux_var(d, cc)];
+      for (int cc = 0; cc < NFL; ++cc) row_put<LL::k5>(&mine[(d * NCHD + cc) * SP + pk[d]], nu[C::flux_var(d, cc)]);
 #pragma unroll
-      for (int cc = 0; cc < NGR; ++cc) mine[(d * NCHD + NFL + cc) * SP + pk[d]] = lG[d][C::grad_var(cc)];
+      for (int cc = 0; cc < NGR; ++cc) row_put<LL::k5>(&mine[(d * NCHD + NFL + cc) * SP + pk[d]], lG[d][C::grad_var(cc)]);
 #pragma unroll
-      for (int cc = 0; cc < NF; ++cc) mine[(NCH + d * NGR + cc) * SP + pk[d]] = fw[cc];
+      for (int cc = 0; cc < NF; ++cc) row_put<LL::k5>(&mine[(NCH + d * NGR + cc) * SP + pk[d]], fw[cc]);
     }
     sync();
     // per cell: adjoint channels (D^T) first, forward channels (D) after
@@ -1783,20 +1783,20 @@ struct LinOp {
         const int d = ch / NCHD, st = LL::lay_B(d);
         double* row = lds + c2 * CELL_ELEMS + ch * SP + LL::addr(d, l, 0);
 #pragma unroll
-        for (int m = 0; m < n; ++m) x[m] = row[m * st];
+        for (int m = 0; m < n; ++m) x[m] = row_get<LL::k5>(&row[m * st]);
         line_deriv_T<double, n>(x, y, inv_h[d]);
 #pragma unroll
-        for (int i = 0; i < n; ++i) row[i * st] = y[i];
+        for (int i = 0; i < n; ++i) row_put<LL::k5>(&row[i * st], y[i]);
       } else if constexpr (NF > 0) {
         const int tf = t - NTA;
         const int l = tf % F, ch = tf / F;
         const int d = ch / NF, st = LL::lay_B(d);
         double* row = lds + c2 * CELL_ELEMS + (NCH + ch) * SP + LL::addr(d, l, 0);
 #pragma unroll
-        for (int m = 0; m < n; ++m) x[m] = row[m * st];
+        for (int m = 0; m < n; ++m) x[m] = row_get<LL::k5>(&row[m * st]);
         line_deriv<double, n>(x, y, inv_h[d]);
 #pragma unroll
-        for (int i = 0; i < n; ++i) row[i * st] = y[i];
+        for (int i = 0; i < n; ++i) row_put<LL::k5>(&row[i * st], y[i]);
       }
     };
     if constexpr (kWave) {
@@ -1821,12 +1821,12 @@ struct LinOp {
         gq[d][v] = 0.0;
       }
 #pragma unroll
-      for (int cc = 0; cc < NFL; ++cc) lF[C::flux_var(d, cc)] = -mine[(d * NCHD + cc) * SP + pk[d]];
+      for (int cc = 0; cc < NFL; ++cc) lF[C::flux_var(d, cc)] = -row_get<LL::k5>(&mine[(d * NCHD + cc) * SP + pk[d]]);
       PDE::flux_T(d, a.pde, lF, mu);
 #pragma unroll
-      for (int cc = 0; cc < NGR; ++cc) mu[C::grad_var(cc)] += mine[(d * NCHD + NFL + cc) * SP + pk[d]];
+      for (int cc = 0; cc < NGR; ++cc) mu[C::grad_var(cc)] += row_get<LL::k5>(&mine[(d * NCHD + NFL + cc) * SP + pk[d]]);
 #pragma unroll
-      for (int cc = 0; cc < NF; ++cc) gq[d][C::grad_var(cc)] = mine[(NCH + d * NGR + cc) * SP + pk[d]];
+      for (int cc = 0; cc < NF; ++cc) gq[d][C::grad_var(cc)] = row_get<LL::k5>(&mine[(NCH + d * NGR + cc) * SP + pk[d]]);
     }
     // no barrier here (see apply)
   }
