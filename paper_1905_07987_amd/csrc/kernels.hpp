@@ -2785,8 +2785,9 @@ struct Launch {
     hipLaunchKernelGGL((bc_flux_kernel<PDE, N>), dim3(1), dim3(64), 0, st, a, tr);
     return hipGetLastError();
   }
-  static bool copies_state(int precision) {
-    return !PDE::kLinear && precision == ADG_FP64 && (Ch::kN64 || Ch::kLineAlways);
+  // (the lane-pair predictor does not copy)
+  static bool copies_state(int precision, long long ncells) {
+    return !PDE::kLinear && precision == ADG_FP64 && (Ch::kLineAlways || !Ch::pair(ncells));
   }
   static const KernelSet* set() {
     static const KernelSet ks = {GP::BLOCK, GP::CPB, GB::CPB,
