@@ -129,9 +129,9 @@ struct GeoA1 {
   // y and z continue on the next banks)
   static constexpr int ROW_X = G::S, ROW_Y = G::n == 5 ? 153 : 228, ROW_Z = G::n == 5 ? 153 : G::S;
   // Elsewhere the rows' accesses are single ones where that was faster: 2-D
-  // (N = 2 .. 7, a step of 6e6 nodes 5 to 9 % less) and 3-D N <= 2 (4 %);
-  // 3-D N = 3 pairs them (1 % the other way).
-  static constexpr bool ALONE = G::DIM == 2 || G::n <= 3 || NODE_ROWS;
+  // (N = 2 .. 7, a step of 6e6 nodes 5 to 9 % less) and 3-D N = 2 (4 %); 3-D
+  // N = 1, 3 pair them (1 % the other way).
+  static constexpr bool ALONE = G::DIM == 2 || G::n == 3 || NODE_ROWS;
   static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;       // per cell, in R
   static_assert(!NODE_ROWS || C::NFLUX * (ROW_X + ROW_Y + ROW_Z) <= C::NCH * G::SP, "rows exceed the cell's LDS");
   static constexpr int FIN_ELEMS = (G::NV + C::NFLUX) * G::SP;   // per cell, in R
@@ -2284,7 +2284,9 @@ __device__ __forceinline__ void surface_terms(const KArgs& a, const double* fl, 
   }
 }
 
-template <class PDE, int N>
+// CELL_LAM: the largest signal speed of every cell's new nodes goes to
+// KArgs::cell_lam (limited steps).
+template <class PDE, int N, bool CELL_LAM = false>
 __global__ void __launch_bounds__((GeoB<PDE, N>::BLOCK))
 correct_kernel(const KArgs a, double* __restrict__ Q, const double* __restrict__ params,
                const double* __restrict__ clock, const double* __restrict__ traces, int next_dt) {
@@ -2328,26 +2330,24 @@ correct_kernel(const KArgs a, double* __restrict__ Q, const double* __restrict__
       qn[v] = (PDE::kLinear ? qold[v] : Q[idx]) - surf[v];
       Q[idx] = qn[v];
     }
-    if (next_dt || (!PDE::kLinear && a.cell_lam)) {
+    if (next_dt || CELL_LAM) {
 #pragma unroll
       for (int d = 0; d < DIM; ++d) lam = lam_max(lam, PDE::max_eigen(qn, P, a.pde, d));
     }
   }
-  if constexpr (!PDE::kLinear) {
-    if (a.cell_lam) {
-      // per-cell maxima: eight lanes fold a cell's nodes
-      red[tid] = lam;
-      __syncthreads();
-      for (int t = tid; t < CPB * 8; t += BLOCK) {
-        const int c2 = t >> 3;
-        double x = 0.0;
-        for (int i = t & 7; i < S; i += 8) x = lam_max(x, red[c2 * S + i]);
+  if constexpr (CELL_LAM) {
+    // per-cell maxima: eight lanes fold a cell's nodes
+    red[tid] = lam;
+    __syncthreads();
+    for (int t = tid; t < CPB * 8; t += BLOCK) {
+      const int c2 = t >> 3;
+      double x = 0.0;
+      for (int i = t & 7; i < S; i += 8) x = lam_max(x, red[c2 * S + i]);
 #pragma unroll
-        for (int off = 4; off > 0; off >>= 1) x = lam_max(x, __shfl_xor(x, off, 64));
-        if ((t & 7) == 0 && cell0 + c2 < ncells) a.cell_lam[cell0 + c2] = x;
-      }
-      __syncthreads();
+      for (int off = 4; off > 0; off >>= 1) x = lam_max(x, __shfl_xor(x, off, 64));
+      if ((t & 7) == 0 && cell0 + c2 < ncells) a.cell_lam[cell0 + c2] = x;
     }
+    __syncthreads();
   }
   if (next_dt) {
     const double m = block_max<BLOCK>(lam, red);
@@ -2712,8 +2712,14 @@ struct Launch {
                             const double* traces, int next_dt, hipStream_t st) {
     KArgs a = a0;
     a.nblocks = blocks_b(a);
-    hipLaunchKernelGGL((correct_kernel<PDE, N>), dim3(a.nblocks), dim3(GB::BLOCK), 0, st, a, Q,
-                       params, clock, traces, next_dt);
+    if constexpr (GeoLim<PDE, N>::built) {
+      if (a.cell_lam)
+        hipLaunchKernelGGL((correct_kernel<PDE, N, true>), dim3(a.nblocks), dim3(GB::BLOCK), 0, st, a, Q, params,
+                           clock, traces, next_dt);
+    }
+    if (!a.cell_lam)
+      hipLaunchKernelGGL((correct_kernel<PDE, N>), dim3(a.nblocks), dim3(GB::BLOCK), 0, st, a, Q, params, clock,
+                         traces, next_dt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kSlots), 0, st, a.slots, a.dt_factor,
