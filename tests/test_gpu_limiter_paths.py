@@ -88,6 +88,45 @@ def test_several_cells_per_wave(dim, cells):
     s.close()
 
 
+def test_captured_limited_steps_replay():
+    """Two limited steps that reuse their ranges, captured and replayed with
+    eager work between the replays: bitwise the run launched step by step
+    (which of the two range arrays is current is kept on the device)."""
+    P, s, Q, sub, st = blast_case(2, 3, [24, 20], [W] * 4, seed=13, radius=0.3)
+    out = []
+    for captured in (False, True):
+        Qg, a, stg = dev(Q), dev(sub), dev(st, torch.uint8)
+        b = torch.zeros_like(a)
+        counts = torch.zeros(3, dtype=torch.int32, device="cuda")
+        clock = torch.zeros(2, dtype=torch.float64, device="cuda")
+        s.stable_dt(Qg, None, clock)
+        kw = dict(next_dt=True, reuse_ranges=True)
+        s.step_limited(Qg, clock, a, b, stg, counts)  # (a new state: nothing to reuse)
+        s.step_limited(Qg, clock, b, a, stg, counts, **kw)
+        torch.cuda.synchronize()
+
+        def pair(stream=None):
+            s.step_limited(Qg, clock, a, b, stg, counts, stream=stream, **kw)
+            s.step_limited(Qg, clock, b, a, stg, counts, stream=stream, **kw)
+
+        hist = []
+        if captured:
+            side = torch.cuda.Stream()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                pair(side.cuda_stream)
+        for _ in range(4):
+            graph.replay() if captured else pair()
+            torch.cuda.synchronize()
+            hist.append((Qg.clone(), stg.clone(), counts.clone(), clock.clone()))
+            float(Qg.sum())  # eager work between the replays
+        out.append(hist)
+    for x, y in zip(*out):
+        assert all(torch.equal(p, q) for p, q in zip(x, y))
+    assert int(out[1][-1][2][1]) > 0
+    s.close()
+
+
 def _dt0(s, Q):
     clock = torch.zeros(2, dtype=torch.float64, device="cuda")
     s.stable_dt(dev(Q), None, clock)
