@@ -155,8 +155,9 @@ struct KernelSet {
   hipError_t (*bc_flux)(const KArgs&, double* bc_trace, hipStream_t);
   // doubles per node of KArgs::keep (0 where the adjoint is not built)
   int keep_slots;
-  // whether predict(precision) on a mesh of ncells cells writes KArgs::qcopy
-  bool (*copies_state)(int precision, long long ncells);
+  // whether predict(precision) on a mesh of ncells cells, with that initial
+  // guess, writes KArgs::qcopy
+  bool (*copies_state)(int precision, long long ncells, int guess);
 };
 
 // Registries implemented by the per-PDE translation units; return nullptr if

@@ -128,10 +128,15 @@ struct GeoA1 {
   // elements of a row of each direction (n = 5: the next channel's lines of
   // y and z continue on the next banks)
   static constexpr int ROW_X = G::S, ROW_Y = G::n == 5 ? 153 : 228, ROW_Z = G::n == 5 ? 153 : G::S;
-  // Elsewhere the rows' accesses are single ones where that was faster: 2-D
-  // (N = 2 .. 7, a step of 6e6 nodes 5 to 9 % less) and 3-D N = 2 (4 %); 3-D
-  // N = 1, 3 pair them (1 % the other way).
-  static constexpr bool ALONE = G::DIM == 2 || G::n == 3 || NODE_ROWS;
+  // Elsewhere the rows' accesses are single ones (the kernel's ALONE) where
+  // that is faster: on 2-D meshes that fill the chip (a step, paired against
+  // single: N = 4, 31000 cells 112.0 and 109.2 us, N = 6 353.8 and 333.2, N =
+  // 3, 612^2 cells 509 and 470); on small ones a wave's chain of single
+  // accesses is longer (N = 3, 4000 cells 18.6 and 33.7 us, N = 6, 4000 cells
+  // 72.0 and 81.8).
+  static constexpr long long kAloneCells =
+      G::DIM != 2 || MF || G::n < 3 ? -1 : (G::n == 3 ? 31000 : (G::n == 4 ? 200000 : 16000));
+  __host__ __device__ static constexpr bool alone(long long ncells) { return kAloneCells >= 0 && ncells >= kAloneCells; }
   static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;       // per cell, in R
   static_assert(!NODE_ROWS || C::NFLUX * (ROW_X + ROW_Y + ROW_Z) <= C::NCH * G::SP, "rows exceed the cell's LDS");
   static constexpr int FIN_ELEMS = (G::NV + C::NFLUX) * G::SP;   // per cell, in R
@@ -418,7 +423,7 @@ __device__ __forceinline__ void pair_put(Pair<float>* p, Pair<float> x) {
   else *p = x;
 }
 
-template <class PDE, int N, class R, bool MF = false>
+template <class PDE, int N, class R, bool MF = false, bool SINGLE = false>
 __global__ void __launch_bounds__((GeoA1<PDE, N, R, MF>::BLOCK), (GeoA1<PDE, N, R, MF>::MIN_WAVES))
 predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ params,
                const double* __restrict__ clock, double* Qout, double* __restrict__ traces) {
@@ -431,6 +436,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
   using GA = GeoA1<PDE, N, R, MF>;
   using T = CT<R, G::n>;
   using P2 = Pair<R>;
+  constexpr bool ALONE = SINGLE || GA::NODE_ROWS;
   constexpr int n = G::n, S = G::S, F = G::F, NV = G::NV, NP = G::NP, DIM = G::DIM;
   constexpr int CPB = GA::CPB, BLOCK = GA::BLOCK, SP = G::SP;
   constexpr int NCH = C::NCH, NCHD = C::NCHD, NFL = C::NFLUX, NGR = C::ngrad();
@@ -548,7 +554,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
               for (int c = 0; c < NFL; ++c) {
                 const int v = C::flux_var(d, c);
                 const P2 x = P2{Fa[d][v], two ? Fb[d][v] : R(0)};
-                pair_put<GA::ALONE>(&mine[row_of(d, c) + pk[d]], x);
+                pair_put<ALONE>(&mine[row_of(d, c) + pk[d]], x);
               }
             }
 #pragma unroll
@@ -613,7 +619,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
           for (int c = cb; c < ce; ++c) {
             P2 x[n];
 #pragma unroll
-            for (int m = 0; m < n; ++m) x[m] = pair_get<GA::ALONE>(&row[c * SP + m]);
+            for (int m = 0; m < n; ++m) x[m] = pair_get<ALONE>(&row[c * SP + m]);
 #pragma unroll
             for (int i = 0; i < n; ++i) {
               R y0 = R(0), y1 = R(0);
@@ -622,7 +628,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
                 y0 += T::D(i, m) * x[m].x;
                 y1 += T::D(i, m) * x[m].y;
               }
-              pair_put<GA::ALONE>(&row[c * SP + i], P2{y0, y1});
+              pair_put<ALONE>(&row[c * SP + i], P2{y0, y1});
             }
           }
         }
@@ -644,7 +650,7 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
           for (int c = 0; c < NFL; ++c) {
             if constexpr (FIN) break;
             const int v = C::flux_var(d, c);
-            const P2 t = pair_get<GA::ALONE>(&mine[row_of(d, c) + pk[d]]);
+            const P2 t = pair_get<ALONE>(&mine[row_of(d, c) + pk[d]]);
             divA[v] = C::first_flux_dir(v) == d ? t.x * ih : fma_r(t.x, ih, divA[v]);
             divB[v] = C::first_flux_dir(v) == d ? t.y * ih : fma_r(t.y, ih, divB[v]);
           }
@@ -2562,6 +2568,11 @@ namespace adg {
 //        64^2 cells packed 28.5 us, one wave 24.7; 80^2 35.4 against 41.0;
 //        N = 6, 64^2 89.6 against 80.8, 80^2 107 against 132; N = 5, 3072
 //        cells: a step 44.4 against 46.0, with a source term 49 against 53).
+//  On 3-D meshes of few cells, too, the time is one block's: N = 3 lines from
+//  kLineCells3 cells on (216 cells: a step 31.1 us against 28.9 on n64; 1000
+//  33.1 against 34.0); N = 4 slice pairs (n64, PACK) below kPackCells3 cells
+//  (216 cells 36.2 against 39.6 in single slices), lane pairs up to
+//  kPairCells (512 cells 42.4 against 46.6).
 //  pair  a lane pair per node (predict_kernel_pair): everything else, and 2-D
 //        meshes of less than kPairCells cells, where the time is that of one
 //        wave's chain and a pair shares its time slices (a step of 256
@@ -2571,7 +2582,11 @@ namespace adg {
 template <class PDE, int N>
 struct Choose64 {
   static constexpr long long kLineCells2 = 15000, kPackCells = N == 5 ? 3000 : 5000;
-  static constexpr long long kPairCells = PDE::DIM != 2 || N < 5 ? 0 : (PDE::kHasSource ? 1800 : (N == 7 ? 768 : 0));
+  static constexpr long long kPairCells = PDE::DIM == 3 ? (N == 4 ? 600 : 0)
+                                          : N < 5       ? 0
+                                                        : (PDE::kHasSource ? 1800 : (N == 7 ? 768 : 0));
+  static constexpr long long kLineCells3 = 700;  // (where lines use the matrix instructions)
+  static constexpr long long kPackCells3 = 300;
   static constexpr bool kLine = GeoLine<PDE, N>::fits && !PDE::kLinear;
   static constexpr bool kLineAlways = kLine && PDE::DIM == 3 && !GeoLine<PDE, N>::MF;
   static constexpr bool kN64 = GeoN64<PDE, N>::fits;
@@ -2579,10 +2594,15 @@ struct Choose64 {
   static constexpr bool kCanPair = !kN64 || kPairCells > 0;
   __host__ __device__ static constexpr bool line(long long ncells, int guess, int iters) {
     if (PDE::DIM == 2) return kLine && ncells >= kLineCells2;
-    return kLineAlways || (kLine && (guess == ADG_GUESS_CERK || iters >= 3));
+    return kLineAlways || (kLine && ncells >= kLineCells3 && (guess == ADG_GUESS_CERK || iters >= 3));
   }
-  __host__ __device__ static constexpr bool pair(long long ncells) { return !kN64 || ncells < kPairCells; }
-  __host__ __device__ static constexpr bool pack(long long ncells) { return kCanPack && ncells >= kPackCells; }
+  __host__ __device__ static constexpr bool pack(long long ncells) {
+    return kCanPack && (PDE::DIM == 2 ? ncells >= kPackCells : ncells < kPackCells3);
+  }
+  // (the lane-pair kernel has no CERK guess)
+  __host__ __device__ static constexpr bool pair(long long ncells, int guess) {
+    return !kN64 || (ncells < kPairCells && !pack(ncells) && guess != ADG_GUESS_CERK);
+  }
 };
 
 }  // namespace adg
@@ -2674,8 +2694,13 @@ struct Launch {
     if (precision == ADG_MIXED_FP32) {
       using GA = GeoA1<PDE, N, float>;
       a.nblocks = blocks_a<GA>(a);
-      hipLaunchKernelGGL((predict_kernel_node<PDE, N, float>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
-                         st, a, Q, params, clock, Qout, traces);
+      constexpr bool both = GA::kAloneCells >= 0;
+      if (both && GA::alone(a.ncells))
+        hipLaunchKernelGGL((predict_kernel_node<PDE, N, float, false, both>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
+                           st, a, Q, params, clock, Qout, traces);
+      else
+        hipLaunchKernelGGL((predict_kernel_node<PDE, N, float>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
+                           st, a, Q, params, clock, Qout, traces);
     } else if (precision == ADG_MIXED_BF16X3) {
       if constexpr (PDE::kLinear) {
         return hipErrorNotSupported;  // refused when the context is created
@@ -2691,7 +2716,7 @@ struct Launch {
       return hipErrorNotSupported;  // not reached
     } else {
       if constexpr (Ch::kCanPair) {
-        if (Ch::pair(a.ncells)) {
+        if (Ch::pair(a.ncells, a.guess)) {
           using GA = GeoA2<PDE, N, double>;
           a.nblocks = blocks_a<GA>(a);
           hipLaunchKernelGGL((predict_kernel_pair<PDE, N, double>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
@@ -2792,8 +2817,8 @@ struct Launch {
     return hipGetLastError();
   }
   // (the lane-pair predictor does not copy)
-  static bool copies_state(int precision, long long ncells) {
-    return !PDE::kLinear && precision == ADG_FP64 && (Ch::kLineAlways || !Ch::pair(ncells));
+  static bool copies_state(int precision, long long ncells, int guess) {
+    return !PDE::kLinear && precision == ADG_FP64 && (Ch::kLineAlways || !Ch::pair(ncells, guess));
   }
   static const KernelSet* set() {
     static const KernelSet ks = {GP::BLOCK, GP::CPB, GB::CPB,

@@ -35,8 +35,11 @@ struct GeoN64 {
   // 6^2 and 7^2 nodes, which leave 14, 28 and 15 lanes of a wave idle that
   // way, five or seven share a block of two or four waves (125 of 128, 252
   // and 245 of 256 lanes).
-  static constexpr int CPB = PACK ? (n == 6 ? 7 : 5) : (S >= 64 ? 1 : 64 / S);
-  static constexpr bool CAN_PACK = DIM == 2 && n >= 5 && n <= 7 && C::NCH <= 8;
+  // In 3-D (n = 5) PACK takes slice pairs (PAIR, below): fewer rounds, for
+  // meshes whose time is that of one block.
+  static constexpr int CPB = PACK && DIM == 2 ? (n == 6 ? 7 : 5) : (S >= 64 ? 1 : 64 / S);
+  static constexpr bool CAN_PACK =
+      DIM == 2 ? n >= 5 && n <= 7 && C::NCH <= 8 : n == 5 && !PDE::kHasNcp && NV <= 5;
   static constexpr int LANES = CPB * S;
   static constexpr int BLOCK = (LANES + 63) / 64 * 64;
   // LDS rows: line-major with the odd line stride of Geo in general (a
@@ -56,7 +59,7 @@ struct GeoN64 {
   // line tasks' access groups (bank cycles of both, odd strides -> these:
   // 2-D n = 7 374 -> 284 per round, ideal 251; n = 6 460 -> 374, ideal 254;
   // 3-D n = 5 180 -> 160, ideal 119)
-  static constexpr bool TIGHT = (DIM == 2 && n < 8) || (DIM == 3 && n == 5);
+  static constexpr bool TIGHT = (DIM == 2 && n < 8) || (DIM == 3 && n == 5 && !PACK);
   static constexpr int LS = PM ? 1 : (TIGHT ? (n == 6 ? 7 : n) : G::LS);  // elements between lines
   static constexpr int ROW_PAD = DIM == 2 && n == 4 ? 1 : 0;
   static constexpr int CELL_PAD = DIM == 2 ? (n == 2 ? 4 : (n == 7 ? 9 : (n == 3 || n == 5 ? 1 : 0))) : 0;
@@ -70,7 +73,7 @@ struct GeoN64 {
   // the waves per CU.  The same holds for two-wave cells of 5^3 nodes (43 KB
   // per block in pairs, 1.5 waves per SIMD): 37 x 26 x 19 cells 0.79 -> 0.63
   // ms per launch.
-  static constexpr bool PAIR = !(DIM == 3 && (n == 4 || n == 5) && !PDE::kHasNcp && NV <= 5);
+  static constexpr bool PAIR = !(DIM == 3 && (n == 4 || (n == 5 && !PACK)) && !PDE::kHasNcp && NV <= 5);
   static constexpr bool FINDIR = !PAIR;
   // Picard rounds' rows: RS elements between rows, EI between a line's points
   static constexpr bool GPM = PM && PAIR;

@@ -113,7 +113,7 @@ adg_status user_traits(const char* source, const std::string& arch, int order, i
                           "(int)adg::UserHasBoundary<AdgUserPDE>::value, "
                           "AdgUserPDE::HAS_NCP ? 0 : ChosenPredictor::line(" + std::to_string(ncells) + "LL, 0, " +
                           std::to_string(iters) + ") ? 3 : ChosenPredictor::pair(" + std::to_string(ncells) +
-                          "LL) ? 0 : ChosenPredictor::pack(" + std::to_string(ncells) + "LL) ? 2 : 1};\n";
+                          "LL, 0) ? 0 : ChosenPredictor::pack(" + std::to_string(ncells) + "LL) ? 2 : 1};\n";
   Compiled c;
   adg_status st = rtc_compile(src, {}, arch, &c, err);
   if (st) return st;

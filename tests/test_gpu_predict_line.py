@@ -77,15 +77,25 @@ def test_step_2d_against_oracle(order, cells, guess, source):
 
 @pytest.mark.parametrize("order,cells", [(5, [54, 55]), (5, [55, 56]), (7, [27, 28]), (7, [28, 28])])
 def test_small_mesh_rules_against_oracle(order, cells):
-    # either side of the counts for lane pairs (N = 7) and packed blocks (N = 5)
+    # either side of the counts for lane pairs (N = 7, which have no CERK guess)
+    # and packed blocks (N = 5)
     test_step_2d_against_oracle(order, cells, "constant", True)
+    test_step_2d_against_oracle(order, cells, "cerk", False)
 
 
-@pytest.mark.parametrize("cells", [[1, 1, 1], [3, 5, 2]])
+@pytest.mark.parametrize("cells", [[1, 1, 1], [3, 5, 2], [7, 8, 7], [9, 9, 8]])
 @pytest.mark.parametrize("iters,guess,source", [(0, "constant", True), (1, "constant", False), (0, "cerk", False)])
 def test_five_cubed_rows_against_oracle(cells, iters, guess, source):
-    # 3-D N = 4, whose rows are laid out a direction at a time
+    # 3-D N = 4: slice pairs, lane pairs, and the rows laid out a direction at a
+    # time, by the number of cells
     test_step_against_oracle(4, cells, iters, guess, source)
+
+
+@pytest.mark.parametrize("iters,guess,source", [(0, "constant", False), (0, "constant", True), (2, "constant", True),
+                                                (3, "cerk", False), (0, "cerk", True)])
+def test_matrix_lines_against_oracle(iters, guess, source):
+    # 3-D N = 3 at a cell count that takes lines, the last wave part full
+    test_step_against_oracle(3, [9, 9, 9], iters, guess, source)
 
 
 @pytest.mark.parametrize("dim,order,cells", [(2, 1, [5, 7]), (2, 4, [7, 3]), (2, 6, [3, 5]), (2, 7, [3, 3]), (3, 2, [3, 2, 5]),
@@ -109,9 +119,8 @@ def test_fp32_rows_against_oracle(dim, order, cells):
     s.close()
 
 
-@pytest.mark.parametrize("order", [1, 2, 3])
-def test_nan_stays_in_its_cell(order):
-    cells = [4, 3, 3]
+@pytest.mark.parametrize("order,cells", [(1, [4, 3, 3]), (2, [4, 3, 3]), (3, [4, 3, 3]), (3, [9, 9, 9])])
+def test_nan_stays_in_its_cell(order, cells):
     s = adg.Solver(3, order, "euler", cells, cfl=0.4)
     P = O.problem(3, order, O.EULER, cells, cfl=0.4)
     Q0 = inputs.smooth_euler_state(O.node_coords(P), 23)
