@@ -491,9 +491,11 @@ predict_kernel_node(const KArgs a, const double* Q, const double* __restrict__ p
   bool src_here = false;
   for (int s = 0; s < a.nsrc; ++s)
     src_here = src_here || (a.src[s].cell >= cell0 && a.src[s].cell < cell0 + CPB);
-  if (src_here && tid < a.nsrc * n) {
-    const int s = tid / n, j = tid - s * n;
-    src_amp[tid] = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + a.t64.xi[j] * dt64);
+  if (src_here) {
+    for (int e = tid; e < a.nsrc * n; e += BLOCK) {
+      const int s = e / n, j = e - s * n;
+      src_amp[e] = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + a.t64.xi[j] * dt64);
+    }
   }
   // (made visible by the first barrier below)
 
@@ -970,9 +972,11 @@ predict_kernel_pair(const KArgs a, const double* Q, const double* __restrict__ p
   bool src_here = false;
   for (int s = 0; s < a.nsrc; ++s)
     src_here = src_here || (a.src[s].cell >= cell0 && a.src[s].cell < cell0 + CPB);
-  if (src_here && tid < a.nsrc * n) {
-    const int s = tid / n, j = tid - s * n;
-    src_amp[tid] = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + a.t64.xi[j] * dt64);
+  if (src_here) {
+    for (int e = tid; e < a.nsrc * n; e += BLOCK) {
+      const int s = e / n, j = e - s * n;
+      src_amp[e] = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + a.t64.xi[j] * dt64);
+    }
   }
   // (made visible by the first barrier below)
 

@@ -225,10 +225,13 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
   bool src_here = false;
   for (int s = 0; s < a.nsrc; ++s)
     src_here = src_here || (a.src[s].cell >= cell0 && a.src[s].cell < cell0 + CPB);
-  if (src_here && tid < a.nsrc * NA) {
-    const int s = tid / NA, j = tid - s * NA;
-    const double tau = j < n ? a.t64.xi[j] : 0.5 * (j - n);
-    src_amp(tid) = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + tau * dt);
+  if (src_here) {
+    // (a block of one wave has fewer threads than 16 sources have entries)
+    for (int e = tid; e < a.nsrc * NA; e += BLOCK) {
+      const int s = e / NA, j = e - s * NA;
+      const double tau = j < n ? a.t64.xi[j] : 0.5 * (j - n);
+      src_amp(e) = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + tau * dt);
+    }
   }
   // (made visible by the first barrier below)
   auto add_point_sources = [&](int j, double* Sv, double sgn = 1.0) {
