@@ -113,32 +113,7 @@ template <class PDE, int N, class R, bool MF = false>
 struct GeoA1 {
   using G = Geo<PDE, N>;
   using C = Chan<PDE>;
-  // 3-D cells of 5^3 and 6^3 nodes: rows without bank conflicts.  An 8-byte
-  // access is served 32 lanes at a time, two rows in one ds_read2 16 lanes of
-  // either; at a line stride of 7 the rows of all three directions straddled
-  // banks (n = 6: 28 % of the LDS cycles).  Here the node threads' 32
-  // consecutive lanes take 32 banks in nearly every access: x and z rows in
-  // node order, point m of y-line l at l + YS m.  Line tasks of x at n = 6
-  // read pairs of neighbours (lines 6 apart: even and odd banks), all others
-  // single elements (consecutive lines, or lines 5 apart).  A predictor, N =
-  // 5, 40^3 cells 3.45 -> 3.00 ms.
-  static constexpr bool NODE_ROWS =
-      !MF && G::DIM == 3 && (G::n == 5 || G::n == 6) && sizeof(R) == 4 && C::ngrad() == 0;
-  static constexpr int YS = G::n == 5 ? 27 : 38;               // between the points of a y-line
-  // elements of a row of each direction (n = 5: the next channel's lines of
-  // y and z continue on the next banks)
-  static constexpr int ROW_X = G::S, ROW_Y = G::n == 5 ? 153 : 228, ROW_Z = G::n == 5 ? 153 : G::S;
-  // Elsewhere the rows' accesses are single ones (the kernel's ALONE) where
-  // that is faster: on 2-D meshes that fill the chip (a step, paired against
-  // single: N = 4, 31000 cells 112.0 and 109.2 us, N = 6 353.8 and 333.2, N =
-  // 3, 612^2 cells 509 and 470); on small ones a wave's chain of single
-  // accesses is longer (N = 3, 4000 cells 18.6 and 33.7 us, N = 6, 4000 cells
-  // 72.0 and 81.8).
-  static constexpr long long kAloneCells =
-      G::DIM != 2 || MF || G::n < 3 ? -1 : (G::n == 3 ? 31000 : (G::n == 4 ? 200000 : 16000));
-  __host__ __device__ static constexpr bool alone(long long ncells) { return kAloneCells >= 0 && ncells >= kAloneCells; }
-  static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;       // per cell, in R
-  static_assert(!NODE_ROWS || C::NFLUX * (ROW_X + ROW_Y + ROW_Z) <= C::NCH * G::SP, "rows exceed the cell's LDS");
+  static constexpr int ITER_ELEMS = C::NCH * G::SP * 2;          // per cell, in R
   static constexpr int FIN_ELEMS = (G::NV + C::NFLUX) * G::SP;   // per cell, in R
   static constexpr int CELL_ELEMS = cmax(ITER_ELEMS, FIN_ELEMS);
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
@@ -149,6 +124,34 @@ struct GeoA1 {
   static constexpr int BLOCK = MF ? (CPB * G::S + 63) / 64 * 64 : CPB * G::S;
   static constexpr int ELEMS = CPB * CELL_ELEMS;
   static_assert(BLOCK >= 64 && BLOCK <= 1024, "block must hold one full wave");
+  // 3-D cells of 5^3 and 6^3 nodes: rows without bank conflicts.  An 8-byte
+  // access is served 32 lanes at a time, two rows in one ds_read2 16 lanes of
+  // either; at a line stride of 7 the rows of all three directions straddled
+  // banks (n = 6: 28 % of the LDS cycles).  Here the node threads' 32
+  // consecutive lanes take 32 banks in nearly every access: x and z rows in
+  // node order, point m of y-line l at l + YS m.  Line tasks of x at n = 6
+  // read pairs of neighbours (lines 6 apart: even and odd banks), all others
+  // single elements (consecutive lines, or lines 5 apart).  A predictor, N =
+  // 5, 40^3 cells 3.45 -> 3.00 ms.
+  // (Every line of a direction is one task, all in one round: run-time PDEs of
+  // more quantities than that leaves threads for, 6 or more at n = 5 and 7 or
+  // more at n = 6, keep the other rows.)
+  static constexpr bool NODE_ROWS = !MF && G::DIM == 3 && (G::n == 5 || G::n == 6) && sizeof(R) == 4 &&
+                                    C::ngrad() == 0 && CPB * C::NFLUX * G::F <= BLOCK;
+  static constexpr int YS = G::n == 5 ? 27 : 38;               // between the points of a y-line
+  // elements of a row of each direction (n = 5: the next channel's lines of
+  // y and z continue on the next banks)
+  static constexpr int ROW_X = G::S, ROW_Y = G::n == 5 ? 153 : 228, ROW_Z = G::n == 5 ? 153 : G::S;
+  static_assert(!NODE_ROWS || C::NFLUX * (ROW_X + ROW_Y + ROW_Z) <= C::NCH * G::SP, "rows exceed the cell's LDS");
+  // Elsewhere the rows' accesses are single ones (the kernel's ALONE) where
+  // that is faster: on 2-D meshes that fill the chip (a step, paired against
+  // single: N = 4, 31000 cells 112.0 and 109.2 us, N = 6 353.8 and 333.2, N =
+  // 3, 612^2 cells 509 and 470); on small ones a wave's chain of single
+  // accesses is longer (N = 3, 4000 cells 18.6 and 33.7 us, N = 6, 4000 cells
+  // 72.0 and 81.8).
+  static constexpr long long kAloneCells =
+      G::DIM != 2 || MF || G::n < 3 ? -1 : (G::n == 3 ? 31000 : (G::n == 4 ? 200000 : 16000));
+  __host__ __device__ static constexpr bool alone(long long ncells) { return kAloneCells >= 0 && ncells >= kAloneCells; }
   // Occupancy target (waves per SIMD) handed to the register allocator:
   // three 4-wave blocks per CU at FP32.
   static constexpr int MIN_WAVES = 3;

@@ -314,3 +314,32 @@ def test_user_source_term_on_either_side_of_the_pair_rule(order, cells):
     torch.cuda.synchronize()
     assert rel_l2(Q.cpu().numpy(), Qo) <= TOL
     s.close()
+
+
+def euler_with_scalars(k):
+    """Euler with k quantities more, densities carried with the flow."""
+    return (EULER3.replace("NV = 5", f"NV = {5 + k}")
+            .replace("F[4] = ud * (Q[4] + p);", f"F[4] = ud * (Q[4] + p); for (int i = 5; i < {5 + k}; ++i) F[i] = ud * Q[i];")
+            .replace("lam[4] = u + c;", f"lam[4] = u + c; for (int i = 5; i < {5 + k}; ++i) lam[i] = u;"))
+
+
+@pytest.mark.parametrize("order,extra", [(4, 0), (4, 1), (4, 3), (5, 1), (5, 2), (5, 3)])
+def test_user_single_precision_with_many_quantities(order, extra):
+    """The FP32 predictor at 5^3 and 6^3 nodes per cell with up to 8 quantities
+    (its rows there depend on how many lines a block has threads for).  Bar:
+    1e-5, that of the mixed-precision predictor, the carried densities being
+    the same multiple of the density after the step."""
+    say("user fp32 quantities", order, 5 + extra)
+    cells = [3, 1, 3]
+    P = O.problem(3, order, O.EULER, cells)
+    Q0 = inputs.smooth_euler_state(O.node_coords(P), 91)
+    f = 0.5 + 0.7 * np.arange(extra)
+    s = adg.Solver(3, order, "euler", cells, source=euler_with_scalars(extra), precision="fp32")
+    Qu, _ = run(s, np.concatenate([Q0, Q0[:, :1] * f[None, :, None]], axis=1), None, 2)
+    Qo, _ = O.run(P, Q0, steps=2)
+    assert rel_l2(Qu[:, :5], Qo) <= 1e-5
+    for i in range(extra):
+        assert rel_l2(Qu[:, 5 + i], f[i] * Qo[:, 0]) <= 1e-5
+    # every cell's increment, not only the mean: no cell took another's rows
+    assert np.abs(Qu[:, :5] - Qo).max() <= 1e-4 * np.abs(Qo - Q0).max()
+    s.close()
