@@ -106,14 +106,12 @@ std::string prelude(const char* source) {
 adg_status user_traits(const char* source, const std::string& arch, int order, int iters, long long ncells,
                        UserTraits* t, std::string* err) {
   const std::string src = prelude(source) +
-                          "using ChosenPredictor = adg::Choose64<adg::UserTerms<AdgUserPDE>, " + std::to_string(order) +
-                          ">;\nextern \"C\" __constant__ int adg_user_traits[8] = {AdgUserPDE::DIM, "
+                          "extern \"C\" __constant__ int adg_user_traits[8] = {AdgUserPDE::DIM, "
                           "AdgUserPDE::NV, AdgUserPDE::NP, (int)AdgUserPDE::LINEAR, "
                           "(int)AdgUserPDE::HAS_NCP, (int)AdgUserPDE::HAS_SOURCE, "
-                          "(int)adg::UserHasBoundary<AdgUserPDE>::value, "
-                          "AdgUserPDE::HAS_NCP ? 0 : ChosenPredictor::line(" + std::to_string(ncells) + "LL, 0, " +
-                          std::to_string(iters) + ") ? 3 : ChosenPredictor::pair(" + std::to_string(ncells) +
-                          "LL, 0) ? 0 : ChosenPredictor::pack(" + std::to_string(ncells) + "LL) ? 2 : 1};\n";
+                          "(int)adg::UserHasBoundary<AdgUserPDE>::value, adg::UserPredictor<AdgUserPDE, " +
+                          std::to_string(order) + ">::of(" + std::to_string(ncells) + "LL, " +
+                          std::to_string(iters) + ")};\n";
   Compiled c;
   adg_status st = rtc_compile(src, {}, arch, &c, err);
   if (st) return st;

@@ -162,4 +162,24 @@ struct Wall<UserTerms<U>> {
   }
 };
 
+// FP64 predictor of a run-time PDE on a mesh of ncells cells (UserTraits::
+// predictor).  A struct whose sizes are refused when the context is created
+// (UserTerms asserts them) and one with a non-conservative product: the lane
+// pair.
+template <class U, int N,
+          bool RULE = (U::DIM == 2 || U::DIM == 3) && U::NV >= 1 && U::NP >= 0 && U::NV + U::NP <= kMaxVar && !U::HAS_NCP>
+struct UserPredictor {
+  static constexpr int of(long long, int) { return 0; }
+};
+template <class U, int N>
+struct UserPredictor<U, N, true> {
+  using Ch = Choose64<UserTerms<U>, N>;
+  static constexpr int of(long long ncells, int iters) {
+    return Ch::line(ncells, ADG_GUESS_CONSTANT, iters) ? 3
+           : Ch::pair(ncells, ADG_GUESS_CONSTANT)      ? 0
+           : Ch::pack(ncells)                          ? 2
+                                                       : 1;
+  }
+};
+
 }  // namespace adg

@@ -343,3 +343,14 @@ def test_user_single_precision_with_many_quantities(order, extra):
     # every cell's increment, not only the mean: no cell took another's rows
     assert np.abs(Qu[:, :5] - Qo).max() <= 1e-4 * np.abs(Qo - Q0).max()
     s.close()
+
+
+@pytest.mark.parametrize("change", [("DIM = 3", "DIM = 4"), ("NV = 5", "NV = 0"), ("NP = 0", "NP = -1"),
+                                    ("NP = 0", "NP = 12")])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_user_sizes_are_an_invalid_argument(change, precision):
+    # the struct's sizes are looked at before anything is compiled for them
+    say("user sizes", change, precision)
+    with pytest.raises(adg.AdgError) as ei:
+        adg.Solver(3, 3, "euler", [3, 2, 2], source=EULER3.replace(*change), precision=precision)
+    assert ei.value.status == -1 and "AdgUserPDE" in str(ei.value)
