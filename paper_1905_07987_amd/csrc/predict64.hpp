@@ -223,8 +223,12 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
     }
   };
   bool src_here = false;
-  for (int s = 0; s < a.nsrc; ++s)
-    src_here = src_here || (a.src[s].cell >= cell0 && a.src[s].cell < cell0 + CPB);
+  unsigned src_mine = 0;  // the sources in this thread's cell (looked up once: each look is a wait for memory)
+  for (int s = 0; s < a.nsrc; ++s) {
+    const long long c = a.src[s].cell;
+    src_here = src_here || (c >= cell0 && c < cell0 + CPB);
+    src_mine |= c == cell && node ? 1u << s : 0u;
+  }
   if (src_here) {
     // (a block of one wave has fewer threads than 16 sources have entries)
     for (int e = tid; e < a.nsrc * NA; e += BLOCK) {
@@ -235,9 +239,9 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
   }
   // (made visible by the first barrier below)
   auto add_point_sources = [&](int j, double* Sv, double sgn = 1.0) {
-    if (!src_here || !node) return;
-    for (int s = 0; s < a.nsrc; ++s) {
-      if (a.src[s].cell != cell) continue;
+    if (!src_here) return;
+    for (unsigned m = src_mine; m; m &= m - 1) {
+      const int s = __builtin_ctz(m);
       const double amp = src_amp(s * NA + j);
       const double* wsk = a.src_w + ((long long)s * S + k) * NV;
 #pragma unroll

@@ -179,9 +179,13 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
   // point sources: the Ricker amplitudes at the n time nodes and at the
   // stage times 0, 1/2, 1 of the CERK guess, where the wave has a source cell
   bool src_here = false;
+  unsigned src_mine = 0;  // the sources in this lane's cell
   if constexpr (MODE == kLineSources)
-    for (int s = 0; s < a.nsrc; ++s)
-      src_here = src_here || (a.src[s].cell >= cell0 && a.src[s].cell < cell0 + CPB);
+    for (int s = 0; s < a.nsrc; ++s) {
+      const long long c = a.src[s].cell;
+      src_here = src_here || (c >= cell0 && c < cell0 + CPB);
+      src_mine |= c == cell && line ? 1u << s : 0u;
+    }
   if (src_here) {
     for (int e = lane; e < a.nsrc * NA; e += 64) {
       const int s = e / NA, j = e - s * NA;
@@ -190,23 +194,24 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
     }
     line_wave_sync();
   }
-  // x[z][v] += scale * (point sources at time entry j)
-  auto add_sources = [&](int j, double scale, double (&x)[n][NV]) {
+  // f(source, node z, its weights there) for the sources of the cell
+  auto each_source = [&](auto f) {
     if (!src_here) return;
-    for (int s = 0; s < a.nsrc; ++s) {
-      if (a.src[s].cell != cell || !line) continue;
-      const double amp = scale * src_amp[s * NA + j];
-      const double* w = a.src_w + ((long long)s * S + l) * NV;
+    for (unsigned m = src_mine; m; m &= m - 1) {
+      const int s = __builtin_ctz(m);
+      const double* ws = a.src_w + ((long long)s * S + l) * NV;
+      double w[n][NV];
 #pragma unroll
       for (int z = 0; z < n; ++z)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) x[z][v] += amp * w[(long long)z * F * NV + v];
+        for (int v = 0; v < NV; ++v) w[z][v] = ws[(long long)z * F * NV + v];
+#pragma unroll
+      for (int z = 0; z < n; ++z) f(s, z, w[z]);
     }
   };
 
-  // R = S - div F of the line's states y (point sources at time entry j, or
-  // none: j < 0)
-  auto rhs = [&](const double (&y)[n][NV], int j, double (&R)[n][NV]) {
+  // R = S - div F of the line's states y, without the point sources
+  auto rhs = [&](const double (&y)[n][NV], double (&R)[n][NV]) {
     double Sv[n][NV];
 #pragma unroll
     for (int z = 0; z < n; ++z) {
@@ -260,7 +265,6 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
 #pragma unroll
         for (int v = 0; v < NV; ++v) R[z][v] += Sv[z][v];
     }
-    if (j >= 0) add_sources(j, 1.0, R);
   };
 
   double q[n][n][NV];  // [time][node of the line][quantity]: the iterate, then its right-hand sides
@@ -271,6 +275,17 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
     for (int v = 0; v < NV; ++v)
 #pragma unroll
       for (int z = 0; z < n; ++z) u[z][v] = Qc[v * S + z * F];
+  };
+  // the point sources of every time node, added to the R_j that q holds
+  auto add_sources = [&]() {
+    each_source([&](int s, int z, const double (&w)[NV]) {
+#pragma unroll
+      for (int j = 0; j < n; ++j) {
+        const double amp = src_amp[s * NA + j];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) q[j][z][v] += amp * w[v];
+      }
+    });
   };
   // q_i = u + dt sum_j KW_ij R_j, R_j held in q[j]
   auto update = [&]() {
@@ -296,7 +311,7 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
 
   const int I = a.picard_iters;
   int r0 = 0;
-    if (MODE == kLineCerk || (MODE == kLineSources && a.guess == ADG_GUESS_CERK)) {
+  if (MODE == kLineCerk || (MODE == kLineSources && a.guess == ADG_GUESS_CERK)) {
     // the continuous extension of the classical Runge-Kutta method on the
     // cell-local ODE, taken at the time nodes (see predict_kernel_n64)
     double Y[n][NV];
@@ -310,7 +325,12 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
       double kk[n][NV];
-      rhs(Y, n + (st == 0 ? 0 : (st == 3 ? 2 : 1)), kk);
+      rhs(Y, kk);
+      each_source([&](int s, int z, const double (&w)[NV]) {
+        const double amp = src_amp[s * NA + n + (st == 0 ? 0 : (st == 3 ? 2 : 1))];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) kk[z][v] += amp * w[v];
+      });
 #pragma unroll
       for (int j = 0; j < n; ++j) {
         const double b = dt * T::cerk_b(st, j);
@@ -331,15 +351,14 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
     // the same right-hand side apart from point sources
     double u[n][NV], R[n][NV];
     load_u(u);
-    rhs(u, -1, R);
+    rhs(u, R);
 #pragma unroll
-    for (int j = 0; j < n; ++j) {
+    for (int j = 0; j < n; ++j)
 #pragma unroll
       for (int z = 0; z < n; ++z)
 #pragma unroll
         for (int v = 0; v < NV; ++v) q[j][z][v] = R[z][v];
-      add_sources(j, 1.0, q[j]);
-    }
+    add_sources();
     update();
     r0 = 1;
   }
@@ -347,12 +366,13 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
 #pragma unroll
     for (int j = 0; j < n; ++j) {
       double R[n][NV];
-      rhs(q[j], j, R);
+      rhs(q[j], R);
 #pragma unroll
       for (int z = 0; z < n; ++z)
 #pragma unroll
         for (int v = 0; v < NV; ++v) q[j][z][v] = R[z][v];
     }
+    add_sources();
     update();
   }
 
@@ -402,8 +422,13 @@ predict_kernel_line(const KArgs a, const double* Q, const double* __restrict__ p
       }
     }
   }
+  each_source([&](int s, int z, const double (&w)[NV]) {
+    double amp = 0.0;
 #pragma unroll
-  for (int j = 0; j < n; ++j) add_sources(j, T::w(j), vol);
+    for (int j = 0; j < n; ++j) amp += T::w(j) * src_amp[s * NA + j];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) vol[z][v] += amp * w[v];
+  });
 
   // Face projection and volume term, an axis at a time.  Along the first XD
   // axes the lane at position p projects the line through node p of the last
