@@ -156,8 +156,8 @@ struct KernelSet {
   // doubles per node of KArgs::keep (0 where the adjoint is not built)
   int keep_slots;
   // whether predict(precision) on a mesh of ncells cells, with that initial
-  // guess, writes KArgs::qcopy
-  bool (*copies_state)(int precision, long long ncells, int guess);
+  // guess and number of Picard passes, writes KArgs::qcopy
+  bool (*copies_state)(int precision, long long ncells, int guess, int iters);
 };
 
 // Registries implemented by the per-PDE translation units; return nullptr if

@@ -719,7 +719,7 @@ adg_status adg_step_limited(adg_ctx* ctx, double* Q, double* clock, const double
   LimWork w = ctx->lim;
   w.reuse = reuse_flag && ctx->lim_ranges_stored ? 1 : 0;
   w.store_next = reuse_flag ? 1 : 0;
-  w.copy = ctx->ks->copies_state(ctx->cfg.precision, ctx->C, ctx->args.guess) ? 0 : 1;
+  w.copy = ctx->ks->copies_state(ctx->cfg.precision, ctx->C, ctx->args.guess, ctx->args.picard_iters) ? 0 : 1;
   ctx->lim_ranges_stored = false;
   hipError_t e = ctx->ks->lim_before(ctx->args, Q, sub_in, status, w, s);
   if (e != hipSuccess) return hip_fail(e, "limiter prepare launch");

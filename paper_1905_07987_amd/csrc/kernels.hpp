@@ -2559,56 +2559,72 @@ count_kernel(unsigned long long* __restrict__ slots, int32_t* __restrict__ count
 namespace adg {
 
 // Which FP64 predictor takes a PDE that is not linear in Q (also used for
-// run-time PDEs):
+// run-time PDEs).  (Times: one step.)
 //  line  one lane per line of nodes (predict_kernel_line): 3-D N <= 3; 2-D
 //        N = 2, 3 from kLineCells2 cells on (fewer, longer waves: N = 3,
 //        100^2 cells 21.3 us against 20.5, 150^2 32.5 against 38.3, 300^2
-//        90 against 118).  Its matrix instructions (3-D N = 3) spread a
-//        non-finite value over a plane of the cell's nodes at once, the LDS
-//        forms along three lines per pass; from three passes on, and after
-//        the four stages of the CERK guess, both have it everywhere in that
-//        cell, so fewer passes stay on the one-thread-per-node kernel.
+//        90 against 118) unless one Picard pass from the constant guess is
+//        all (N = 2, 260^2 cells 51.8 us against 49.6).  Its matrix
+//        instructions (3-D N = 3) spread a non-finite value over a plane of
+//        the cell's nodes at once, the LDS forms along three lines per pass;
+//        from three passes on, and after the four stages of the CERK guess,
+//        both have it everywhere in that cell, so fewer passes stay on the
+//        one-thread-per-node kernel.
 //  n64   one thread per node (predict_kernel_n64) where a cell fits one block
 //        of at most four waves; 2-D cells of 5^2 .. 7^2 nodes packed into
 //        blocks of several waves from kPackCells cells on (below, all waves
 //        are on the chip at once and what counts is the time of one: N = 4,
 //        64^2 cells packed 28.5 us, one wave 24.7; 80^2 35.4 against 41.0;
 //        N = 6, 64^2 89.6 against 80.8, 80^2 107 against 132; N = 5, 3072
-//        cells: a step 44.4 against 46.0, with a source term 49 against 53).
-//  On 3-D meshes of few cells, too, the time is one block's: N = 3 lines from
-//  kLineCells3 cells on (216 cells: a step 31.1 us against 28.9 on n64; 1000
-//  33.1 against 34.0); N = 4 slice pairs (n64, PACK) below kPackCells3 cells
-//  (216 cells 36.2 against 39.6 in single slices), lane pairs up to
-//  kPairCells (512 cells 42.4 against 46.6).
-//  pair  a lane pair per node (predict_kernel_pair): everything else, and 2-D
-//        meshes of less than kPairCells cells, where the time is that of one
-//        wave's chain and a pair shares its time slices (a step of 256
-//        cells: Euler N = 7 36.7 us against 40.6, N = 6 37.7 against 35.1; a
-//        PDE with a source term N = 5 30.4 against 32.4, N = 6 38.7 against
-//        43.5, N = 7 41.9 against 51.7; 2048 cells, N = 7: 84 against 78).
+//        cells: 44.4 against 46.0, with a source term 49 against 53).
+//  pair  a lane pair per node (predict_kernel_pair): everything else, and
+//        meshes of few cells (below).
+// On meshes of few cells the time is that of one block's chain:
+//  3-D N = 2, CERK guess  lines from 4000 cells on, 5800 with point sources
+//        (whose cells' blocks take longer): 12^3 cells 28.4 us against 25.7,
+//        16^3 32.4 against 40.6; nine sources in a cell, 16^3 44.3 against
+//        42.4, 18^3 53.0 against 52.9, 20^3 56.1 against 68.3.
+//  3-D N = 3  lines from 700 cells on (216 cells: 31.1 us against 28.9 on n64;
+//        1000 33.1 against 34.0), with the CERK guess from 1200 (729 cells
+//        25.1 against 24.6, 11^3 26.5 against 28.3), from 2000 with point
+//        sources too (12^3 30.0 against 29.7, 13^3 35.8 against 37.5).
+//  3-D N = 4  slice pairs (n64, PACK) below kPackCells3 cells (216 cells 36.2
+//        us against 39.6 in single slices), lane pairs from there to
+//        kPairCells, two blocks on every compute unit (512 cells 38.7 against
+//        41.9; 576 cells 65.9 against 44.1), from kPairIters passes on (one
+//        pass: 18.9 against 17.6).
+//  2-D N = 7  lane pairs, which share a node's time slices, up to kPairCells
+//        cells (256 cells 35.1 us against 39.0, 729 45.6 against 44.1) from
+//        kPairIters passes on (256 cells, five passes 26.6 against 27.1, four
+//        23.7 against 23.2); at N = 6 they are slower (256 cells 37.7 against
+//        35.1).  A PDE with a source term: from N = 5 on up to 1800 cells
+//        (256 cells N = 5 30.4 against 32.4, N = 6 38.7 against 43.5, N = 7
+//        41.9 against 51.7; 2048 cells, N = 7: 84 against 78).
 template <class PDE, int N>
 struct Choose64 {
+  static constexpr bool kSource2 = PDE::DIM == 2 && N >= 5 && PDE::kHasSource;
   static constexpr long long kLineCells2 = 15000, kPackCells = N == 5 ? 3000 : 5000;
-  static constexpr long long kPairCells = PDE::DIM == 3 ? (N == 4 ? 600 : 0)
-                                          : N < 5       ? 0
-                                                        : (PDE::kHasSource ? 1800 : (N == 7 ? 768 : 0));
-  static constexpr long long kLineCells3 = 700;  // (where lines use the matrix instructions)
+  static constexpr long long kPairCells = kSource2 ? 1800 : ((PDE::DIM == 3 ? N == 4 : N == 7) ? 512 : 0);
+  static constexpr int kPairIters = kSource2 ? 1 : (PDE::DIM == 3 ? 2 : 5);
   static constexpr long long kPackCells3 = 300;
   static constexpr bool kLine = GeoLine<PDE, N>::fits && !PDE::kLinear;
-  static constexpr bool kLineAlways = kLine && PDE::DIM == 3 && !GeoLine<PDE, N>::MF;
+  static constexpr bool kLineAlways = kLine && PDE::DIM == 3 && N == 1;
   static constexpr bool kN64 = GeoN64<PDE, N>::fits;
   static constexpr bool kCanPack = kN64 && GeoN64<PDE, N>::CAN_PACK;
   static constexpr bool kCanPair = !kN64 || kPairCells > 0;
-  __host__ __device__ static constexpr bool line(long long ncells, int guess, int iters) {
-    if (PDE::DIM == 2) return kLine && ncells >= kLineCells2;
-    return kLineAlways || (kLine && ncells >= kLineCells3 && (guess == ADG_GUESS_CERK || iters >= 3));
+  __host__ __device__ static constexpr bool line(long long ncells, int guess, int iters, int nsrc) {
+    const bool cerk = guess == ADG_GUESS_CERK;
+    if (!kLine || kLineAlways) return kLine;
+    if (PDE::DIM == 2) return ncells >= kLineCells2 && (cerk || iters >= 2);
+    if (N == 2) return !cerk || ncells >= (nsrc ? 5800 : 4000);
+    return cerk ? ncells >= (nsrc ? 2000 : 1200) : ncells >= 700 && iters >= 3;
   }
   __host__ __device__ static constexpr bool pack(long long ncells) {
     return kCanPack && (PDE::DIM == 2 ? ncells >= kPackCells : ncells < kPackCells3);
   }
   // (the lane-pair kernel has no CERK guess)
-  __host__ __device__ static constexpr bool pair(long long ncells, int guess) {
-    return !kN64 || (ncells < kPairCells && !pack(ncells) && guess != ADG_GUESS_CERK);
+  __host__ __device__ static constexpr bool pair(long long ncells, int guess, int iters) {
+    return !kN64 || (ncells <= kPairCells && !pack(ncells) && guess != ADG_GUESS_CERK && iters >= kPairIters);
   }
 };
 
@@ -2717,13 +2733,11 @@ struct Launch {
         hipLaunchKernelGGL((predict_kernel_node<PDE, N, float, true>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
                            st, a, Q, params, clock, Qout, traces);
       }
-    } else if (Ch::line(a.ncells, a.guess, a.picard_iters)) {
+    } else if (Ch::line(a.ncells, a.guess, a.picard_iters, a.nsrc)) {
       launch_line(a, Q, params, clock, Qout, traces, st);
-    } else if constexpr (Ch::kLineAlways) {
-      return hipErrorNotSupported;  // not reached
-    } else {
+    } else if constexpr (!Ch::kLineAlways) {
       if constexpr (Ch::kCanPair) {
-        if (Ch::pair(a.ncells, a.guess)) {
+        if (Ch::pair(a.ncells, a.guess, a.picard_iters)) {
           using GA = GeoA2<PDE, N, double>;
           a.nblocks = blocks_a<GA>(a);
           hipLaunchKernelGGL((predict_kernel_pair<PDE, N, double>), dim3(a.nblocks), dim3(GA::BLOCK), 0,
@@ -2824,8 +2838,8 @@ struct Launch {
     return hipGetLastError();
   }
   // (the lane-pair predictor does not copy)
-  static bool copies_state(int precision, long long ncells, int guess) {
-    return !PDE::kLinear && precision == ADG_FP64 && (Ch::kLineAlways || !Ch::pair(ncells, guess));
+  static bool copies_state(int precision, long long ncells, int guess, int iters) {
+    return !PDE::kLinear && precision == ADG_FP64 && !Ch::pair(ncells, guess, iters);
   }
   static const KernelSet* set() {
     static const KernelSet ks = {GP::BLOCK, GP::CPB, GB::CPB,

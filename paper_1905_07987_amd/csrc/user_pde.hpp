@@ -175,10 +175,10 @@ template <class U, int N>
 struct UserPredictor<U, N, true> {
   using Ch = Choose64<UserTerms<U>, N>;
   static constexpr int of(long long ncells, int iters) {
-    return Ch::line(ncells, ADG_GUESS_CONSTANT, iters) ? 3
-           : Ch::pair(ncells, ADG_GUESS_CONSTANT)      ? 0
-           : Ch::pack(ncells)                          ? 2
-                                                       : 1;
+    return Ch::line(ncells, ADG_GUESS_CONSTANT, iters, 0) ? 3
+           : Ch::pair(ncells, ADG_GUESS_CONSTANT, iters)  ? 0
+           : Ch::pack(ncells)                             ? 2
+                                                          : 1;
   }
 };
 

@@ -136,3 +136,32 @@ def test_nan_stays_in_its_cell(order, cells):
     assert torch.equal(out[keep], ref[keep]) and bool(torch.isfinite(tr[keep]).all())
     assert bool(torch.isnan(out[13, 0]).any())
     s.close()
+
+
+@pytest.mark.parametrize("order,cells,iters,guess,source", [
+    (2, [19, 14, 15], 0, "cerk", False), (2, [20, 20, 10], 0, "cerk", False),
+    (2, [17, 31, 11], 0, "cerk", True), (2, [20, 29, 10], 0, "cerk", True),
+    (3, [10, 17, 7], 0, "cerk", False), (3, [10, 12, 10], 0, "cerk", False),
+    (3, [9, 13, 17], 0, "cerk", True), (3, [10, 20, 10], 0, "cerk", True),
+    (4, [8, 8, 8], 1, "constant", False), (4, [8, 8, 8], 2, "constant", True), (4, [3, 9, 19], 2, "constant", True)])
+def test_three_dimensional_rules_against_oracle(order, cells, iters, guess, source):
+    # either side of the cell counts and passes for lines (N = 2, 3 with the
+    # CERK guess) and lane pairs (N = 4)
+    test_step_against_oracle(order, cells, iters, guess, source)
+
+
+@pytest.mark.parametrize("order,cells,iters", [(7, [16, 32], 4), (7, [16, 32], 5), (7, [19, 27], 5), (2, [125, 120], 1),
+                                               (2, [125, 120], 2), (3, [125, 120], 1)])
+def test_two_dimensional_rules_against_oracle(order, cells, iters):
+    # either side of the cells and passes for lane pairs and for lines
+    print("[gpu-test] 2-D rules", order, cells, iters, flush=True)
+    P = O.problem(2, order, O.EULER, cells, cfl=0.4, picard_iters=iters)
+    s = adg.Solver(2, order, "euler", cells, cfl=0.4, picard_iters=iters)
+    Q0 = inputs.smooth_euler_state(O.node_coords(P), 31)
+    dt = O.stable_dt(P, Q0)[0]
+    Qo = O.step(P, Q0, None, dt, 0.0)
+    Q, clock = dev(Q0), dev([0.0, dt])
+    s.step(Q, None, clock, next_dt=False)
+    torch.cuda.synchronize()
+    assert rel_l2(Q.cpu().numpy(), Qo) <= TOL
+    s.close()
