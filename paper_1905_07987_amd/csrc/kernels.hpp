@@ -204,8 +204,7 @@ struct GeoA2 {
   static constexpr int CPB = cmin(by_threads, by_lds);
   static constexpr int BLOCK = CPB * TPC;
   static constexpr int ELEMS = CPB * CELL_ELEMS;
-  static_assert(BLOCK >= 64 && BLOCK <= 1024, "block must hold one full wave");
-  static_assert(ELEMS * (int)sizeof(R) <= 64 * 1024, "predictor LDS exceeds 64 KiB");
+  static constexpr bool fits = BLOCK >= 64 && BLOCK <= 1024 && ELEMS * (int)sizeof(R) <= 64 * 1024;
   // A one-cell block of seven or more waves runs one block per CU at the register
   // counts of this kernel (at most 3 waves/SIMD), so they can afford a
   // second LDS buffer (gfx950: 160 KiB per CU): chunk steps alternate
@@ -902,6 +901,8 @@ predict_kernel_pair(const KArgs a, const double* Q, const double* __restrict__ p
   using GA = GeoA2<PDE, N, R>;
   using T = CT<R, G::n>;
   using P2 = Pair<R>;
+  static_assert(GA::BLOCK >= 64 && GA::BLOCK <= 1024, "block must hold one full wave");
+  static_assert(GA::ELEMS * (int)sizeof(R) <= 64 * 1024, "predictor LDS exceeds 64 KiB");
   constexpr int n = G::n, S = G::S, F = G::F, NV = G::NV, NP = G::NP, DIM = G::DIM;
   constexpr int CPB = GA::CPB, BLOCK = GA::BLOCK, SP = GA::SP, H = GA::H, TPC = GA::TPC;
   constexpr int NCHD = C::NCHD, NFL = C::NFLUX, NGR = C::ngrad();

@@ -163,9 +163,27 @@ struct Wall<UserTerms<U>> {
 };
 
 // FP64 predictor of a run-time PDE on a mesh of ncells cells (UserTraits::
-// predictor).  A struct whose sizes are refused when the context is created
-// (UserTerms asserts them) and one with a non-conservative product: the lane
-// pair.
+// predictor): the kernel that Choose64 names where it was measured against the
+// lane pair (1 to 12 quantities, Burgers and Euler with carried densities, with
+// and without a source term) and is faster, else the lane pair.  It keeps the
+// lane pair
+//  - in 2-D with a source term at N = 5 from 5 quantities on, N = 6 at 6 and 7,
+//    N = 7 from 4 on: one thread holds all time slices and the source's, and
+//    spills (a step of 130^2 cells, lane pairs against one thread per node: N =
+//    5, 4 quantities 260 and 162 us, 5 297 and 340, 8 550 and 1136; N = 6, 5
+//    769 and 624, 6 860 and 1031, 8 1240 and 1092; N = 7, 3 427 and 341, 4 549
+//    and 597, 8 1254 and 1776);
+//  - in 3-D at N = 3 on meshes of less than 1200 cells (up to 5 quantities;
+//    1000 cells 33.4 and 36.0 us at 5, 24.1 both at 4, 1728 cells 49.2 and
+//    37.7), at N = 4 of 300 to 1500 cells with one quantity (1331 cells 26.5
+//    and 28.2, 1728 32.8 and 29.8) and with 4 or 5 and a source term (20^3 cells, 5 quantities 526
+//    and 612), at N = 5 up to 256 cells (216: 39.7 and 43.5 at 5 quantities),
+//    up to 600 with two (512: 30.1 and 31.2), and with a source term from 4
+//    quantities on (20^3 cells, 5 quantities 1073 and 1566);
+//  - where the lane pair's LDS does not fit (a context that was refused before
+//    other kernels took run-time PDEs is refused still), where the struct's
+//    sizes are refused when the context is created (UserTerms asserts them),
+//    and with a non-conservative product.
 template <class U, int N,
           bool RULE = (U::DIM == 2 || U::DIM == 3) && U::NV >= 1 && U::NP >= 0 && U::NV + U::NP <= kMaxVar && !U::HAS_NCP>
 struct UserPredictor {
@@ -174,11 +192,21 @@ struct UserPredictor {
 template <class U, int N>
 struct UserPredictor<U, N, true> {
   using Ch = Choose64<UserTerms<U>, N>;
+  static constexpr int NV = U::NV;
+  static constexpr bool pair(long long ncells, int iters) {
+    if (!GeoA2<UserTerms<U>, N, double>::fits || Ch::pair(ncells, ADG_GUESS_CONSTANT, iters)) return true;
+    if (U::DIM == 2) return U::HAS_SOURCE && (N == 5 ? NV >= 5 : (N == 6 ? NV == 6 || NV == 7 : N == 7 && NV >= 4));
+    if (N == 3) return NV <= 5 && ncells < 1200;
+    if (N == 4)
+      return ncells >= 300 && ((NV == 1 && ncells < 1500) || (U::HAS_SOURCE && (NV == 4 || NV == 5)));
+    if (N == 5) return ncells <= 256 || (NV == 2 && ncells < 600) || (U::HAS_SOURCE && NV >= 4);
+    return false;
+  }
   static constexpr int of(long long ncells, int iters) {
-    return Ch::line(ncells, ADG_GUESS_CONSTANT, iters, 0) ? 3
-           : Ch::pair(ncells, ADG_GUESS_CONSTANT, iters)  ? 0
-           : Ch::pack(ncells)                             ? 2
-                                                          : 1;
+    return pair(ncells, iters)                               ? 0
+           : Ch::line(ncells, ADG_GUESS_CONSTANT, iters, 0)  ? 3
+           : Ch::pack(ncells)                                ? 2
+                                                             : 1;
   }
 };
 
