@@ -235,6 +235,7 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
       const int s = e / NA, j = e - s * NA;
       const double tau = j < n ? a.t64.xi[j] : 0.5 * (j - n);
       src_amp(e) = ricker(a.src[s].f0, a.src[s].t0, a.src[s].amp, t_n + tau * dt);
+      if constexpr (BLOCK >= kMaxSources * NA) break;
     }
   }
   // (made visible by the first barrier below)
