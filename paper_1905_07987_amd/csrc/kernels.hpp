@@ -1685,6 +1685,9 @@ struct LinOp {
                                : along_z(ln.mz, t[v]);
       }
     }
+    // (one row set: the next application's writes stay behind the other
+    // lanes' reads; a fence within the wave, no instruction)
+    if constexpr (LG::SETS == 1) sync();
     if constexpr (PDE::kHasNcp) PDE::ncp(t, P, a.pde, g, B);
     if constexpr (PDE::kHasSource) PDE::source(t, P, a.pde, Sv);
 #pragma unroll
@@ -1754,6 +1757,7 @@ struct LinOp {
                             : along_z(ln.mz, fw[cc]);
       }
     }
+    if constexpr (LG::SETS == 1) sync();  // (as in apply_gather)
   }
 
   // mu = L^T nu at this node (FP64; the PDE's transposes): the flux part
