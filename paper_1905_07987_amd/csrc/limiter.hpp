@@ -273,75 +273,95 @@ inline int lim_cells_per_wave(long long ncells) {
   return p < 1 ? 1 : (p > 16 ? 16 : (int)p);
 }
 
+// What prepare does for cell c, of status st at t^n, on one wave: u^n copied
+// (w.copy), the range of its subcell averages into lohi.
 template <class PDE, int N>
-__global__ void __launch_bounds__(256)
-lim_prepare_kernel(const KArgs a, const double* __restrict__ Q, const double* __restrict__ sub_in,
-                   const uint8_t* __restrict__ status, const LimWork w, int per) {
+__device__ __forceinline__ void lim_prepare_cell(const KArgs& a, const double* __restrict__ Q,
+                                                 const double* __restrict__ sub_in, const LimWork& w, double* lohi,
+                                                 long long c, int st, double* ra, int lane) {
   using GL = GeoLim<PDE, N>;
   using GW = GeoLimW<PDE, N>;
   constexpr int NV = GL::NV, S = GL::S, NS = GL::NS, m = GL::m;
+  double* rb = ra + GW::RA;
+  double* rn = rb + GW::RB;
+  double x[NV];
+  lim_load_nodes<PDE, N>(Q, c, a.ncells, lane, x);
+  if (w.copy && lane < S)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) w.Qold[(c * NV + v) * S + lane] = x[v];
+  if (w.reuse && st == 0) return;
+  double lo[NV], hi[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    lo[v] = INFINITY;
+    hi[v] = -INFINITY;
+  }
+  if (st >= 2) {
+    for (int s = lane; s < NS; s += 64)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const double y = sub_in[(c * NV + v) * NS + s];
+        lo[v] = fmin(lo[v], y);
+        hi[v] = fmax(hi[v], y);
+      }
+  } else {
+    lim_stage_nodes<PDE, N>(x, ra, rn, lane);
+    double q[NV][m];
+    lim_group_wave<PDE, N, 0, GW::VG>(ra, ra, rb, lane, q);
+    lim_group_wave<PDE, N, GW::VG, NV - GW::VG>(rn, ra, rb, lane, q);
+    if (lane < GW::LAST)
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int j = 0; j < m; ++j) {
+          lo[v] = fmin(lo[v], q[v][j]);
+          hi[v] = fmax(hi[v], q[v][j]);
+        }
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const double l = lim_wave_min(lo[v]), h = lim_wave_max(hi[v]);
+    if (lane == 0) {
+      lohi[(c * NV + v) * 2] = l;
+      lohi[(c * NV + v) * 2 + 1] = h;
+    }
+  }
+}
+
+// ONE: a wave per cell (per == 1), without the loop, out of which the
+// projection's constants are moved into scalar registers and spilled (2-D N =
+// 7, 256 cells: 7.6 us, 12.1 us with the loop).
+template <class PDE, int N, bool ONE>
+__global__ void __launch_bounds__(256)
+lim_prepare_kernel(const KArgs a, const double* __restrict__ Q, const double* __restrict__ sub_in,
+                   const uint8_t* __restrict__ status, const LimWork w, int per) {
+  using GW = GeoLimW<PDE, N>;
+  constexpr int NV = GeoLim<PDE, N>::NV;
   __shared__ double buf[GW::WPB][GW::PW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (blockIdx.x == 0 && tid < 4) w.counters[tid] = 0;
-  const long long first = (long long)blockIdx.x * GW::WPB + wv, waves = (a.ncells + per - 1) / per;
-  if (first >= waves) return;
+  const long long first = (long long)blockIdx.x * GW::WPB + wv;
   double* const lohi = w.lohi2 + *w.parity * (a.ncells * (NV * 2));
-  double* ra = buf[wv];
-  double* rb = ra + GW::RA;
-  double* rn = rb + GW::RB;
-  uint8_t mine = 0;  // lane i: status of the wave's cell i
-  const long long mc = first + lane * waves;
-  if (lane < per && mc < a.ncells) {
-    mine = status[mc];
-    w.st_prev[mc] = mine;
-  }
-  unsigned long long todo = __ballot(lane < per && mc < a.ncells && (!w.reuse || w.copy || mine != 0));
-  while (todo) {
-    const int i = __ffsll(todo) - 1;
-    todo &= todo - 1;
-    const long long c = first + i * waves;
-    const int st = __shfl((int)mine, i, 64);
-    double x[NV];
-    lim_load_nodes<PDE, N>(Q, c, a.ncells, lane, x);
-    if (w.copy && lane < S)
-#pragma unroll
-      for (int v = 0; v < NV; ++v) w.Qold[(c * NV + v) * S + lane] = x[v];
-    if (w.reuse && st == 0) continue;
-    double lo[NV], hi[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      lo[v] = INFINITY;
-      hi[v] = -INFINITY;
+  if constexpr (ONE) {
+    if (first >= a.ncells) return;
+    const uint8_t st = status[first];
+    if (lane == 0) w.st_prev[first] = st;
+    if (!w.reuse || w.copy || st != 0)
+      lim_prepare_cell<PDE, N>(a, Q, sub_in, w, lohi, first, st, buf[wv], lane);
+  } else {
+    const long long waves = (a.ncells + per - 1) / per;
+    if (first >= waves) return;
+    uint8_t mine = 0;  // lane i: status of the wave's cell i
+    const long long mc = first + lane * waves;
+    if (lane < per && mc < a.ncells) {
+      mine = status[mc];
+      w.st_prev[mc] = mine;
     }
-    if (st >= 2) {
-      for (int s = lane; s < NS; s += 64)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const double y = sub_in[(c * NV + v) * NS + s];
-          lo[v] = fmin(lo[v], y);
-          hi[v] = fmax(hi[v], y);
-        }
-    } else {
-      lim_stage_nodes<PDE, N>(x, ra, rn, lane);
-      double q[NV][m];
-      lim_group_wave<PDE, N, 0, GW::VG>(ra, ra, rb, lane, q);
-      lim_group_wave<PDE, N, GW::VG, NV - GW::VG>(rn, ra, rb, lane, q);
-      if (lane < GW::LAST)
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-#pragma unroll
-          for (int j = 0; j < m; ++j) {
-            lo[v] = fmin(lo[v], q[v][j]);
-            hi[v] = fmax(hi[v], q[v][j]);
-          }
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const double l = lim_wave_min(lo[v]), h = lim_wave_max(hi[v]);
-      if (lane == 0) {
-        lohi[(c * NV + v) * 2] = l;
-        lohi[(c * NV + v) * 2 + 1] = h;
-      }
+    unsigned long long todo = __ballot(lane < per && mc < a.ncells && (!w.reuse || w.copy || mine != 0));
+    while (todo) {
+      const int i = __ffsll(todo) - 1;
+      todo &= todo - 1;
+      lim_prepare_cell<PDE, N>(a, Q, sub_in, w, lohi, first + i * waves, __shfl((int)mine, i, 64), buf[wv], lane);
     }
   }
 }
@@ -509,7 +529,11 @@ lim_detect_kernel(const KArgs a, const double* __restrict__ Q, const LimWork w) 
 // of subcells, one per lane (N = 5: 11 of 64 lanes with a wave per cell).  A
 // lane contracts the nodes with its column's row of A along x (nodes in LDS,
 // the same for all lanes of a cell), then along y in registers.  (81^2 cells,
-// N = 5: 13.8 us, 26 us with a wave per cell.)
+// N = 5: 13.8 us, 26 us with a wave per cell.)  On meshes that leave the chip
+// idle a cell's chain counts, which is shorter on a wave of its own where the
+// cells are large (N = 5, 6, 7: 256 cells 13.4, 14.0 and 16.1 us, a wave per
+// cell 11.2, 11.9 and 13.3; 1600 cells 12.5, 13.6 and 15.9, 11.8, 13.3 and
+// 15.0): kAlone.
 template <class PDE, int N>
 struct GeoDet2 {
   using GL = GeoLim<PDE, N>;
@@ -518,6 +542,7 @@ struct GeoDet2 {
   static constexpr int WPB = 4;
   // doubles of LDS per cell: the nodes (an odd stride), then the columns' ranges
   static constexpr int CELL = cmax(NV * S, 2 * NV * m) | 1;
+  static constexpr long long kAlone = N >= 5 ? 2000 : 0;  // a wave per cell below this many cells
   static unsigned grid(long long ncells) { return (unsigned)((ncells + CPW * WPB - 1) / (CPW * WPB)); }
 };
 
@@ -1272,20 +1297,25 @@ struct LimLaunch {
                            const LimWork& w, hipStream_t st) {
     const int per = w.reuse && !w.copy ? lim_cells_per_wave(a.ncells) : 1;
     const unsigned grid = GeoLimSeq<PDE, N>::grid((a.ncells + per - 1) / per);
-    hipLaunchKernelGGL((lim_prepare_kernel<PDE, N>), dim3(grid), dim3(64 * GeoLimW<PDE, N>::WPB), 0, st, a, Q,
-                       sub_in, status, w, per);
+    const auto k = per == 1 ? lim_prepare_kernel<PDE, N, true> : lim_prepare_kernel<PDE, N, false>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * GeoLimW<PDE, N>::WPB), 0, st, a, Q, sub_in, status, w, per);
     return hipGetLastError();
   }
   // detect, classify, FV cells, DG cells with FV faces
   static hipError_t after(const KArgs& a, double* Q, double* clock, const double* traces,
                           const double* sub_in, double* sub_out, uint8_t* status, const LimWork& w,
                           int next_dt, hipStream_t st) {
+    bool packed = false;
     if constexpr (GL::DIM == 2) {
       using GD = GeoDet2<PDE, N>;
-      hipLaunchKernelGGL((lim_detect2_kernel<PDE, N>), dim3(GD::grid(a.ncells)), dim3(64 * GD::WPB), 0, st, a, Q, w);
-    } else {
-      hipLaunchKernelGGL((lim_detect_kernel<PDE, N>), dim3(GeoLimSeq<PDE, N>::grid(a.ncells)),
-                         dim3(64 * GeoLimW<PDE, N>::WPB), 0, st, a, Q, w);
+      packed = a.ncells >= GD::kAlone;
+      if (packed)
+        hipLaunchKernelGGL((lim_detect2_kernel<PDE, N>), dim3(GD::grid(a.ncells)), dim3(64 * GD::WPB), 0, st, a, Q, w);
+    }
+    if constexpr (GL::DIM == 3 || N >= 5) {
+      if (!packed)
+        hipLaunchKernelGGL((lim_detect_kernel<PDE, N>), dim3(GeoLimSeq<PDE, N>::grid(a.ncells)),
+                           dim3(64 * GeoLimW<PDE, N>::WPB), 0, st, a, Q, w);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -132,3 +132,9 @@ def _dt0(s, Q):
     s.stable_dt(dev(Q), None, clock)
     torch.cuda.synchronize()
     return s.read_clock(clock)[1]
+
+
+@pytest.mark.parametrize("order,cells", [(5, [49, 40]), (5, [50, 41]), (7, [45, 45])])
+def test_packed_detection_at_high_order(order, cells):
+    # either side of the cell count from which 2-D cells of N >= 5 share a wave
+    test_every_split_matches_the_oracle(2, order, cells, [W] * 4)
