@@ -42,10 +42,9 @@ template <class PDE, int N>
 struct GeoLim {
   static constexpr int DIM = PDE::DIM, NV = PDE::NV, n = N + 1, m = 2 * N + 1;
   static constexpr int S = ipow(n, DIM), F = ipow(n, DIM - 1);
-  static constexpr int NS = ipow(m, DIM), NSF = ipow(m, DIM - 1);
+  static constexpr int NS = ipow(m, DIM);
   static constexpr int EB = m + 4, NB = ipow(EB, DIM);  // subcells of the cell and two ghost layers
   static constexpr int EC = m + 2, NC = ipow(EC, DIM);  // subcells whose face values are moved
-  static constexpr int NTAB = m * n;                    // A [m][n]
   // threads of the FV kernel: its phases in one round each where that fits
   // (3-D N = 3: 720 lines along x, 729 subcells with moved faces)
   static constexpr int BLOCK = DIM == 2 ? 256 : (N == 3 ? 768 : (N == 2 ? 512 : 256));
@@ -61,7 +60,7 @@ struct GeoLim {
   static constexpr int FIT = NV * (NS + ipow(m, DIM - 1) * n) + 2 * DIM * NV * ipow(m, DIM - 2) * n;
   static constexpr int REG_A = cmax(T1, cmax(NV * NB, FIT));
   static constexpr int REG_B = cmax(T2, NV * (NC + DIM * NFC));
-  static constexpr int FV_D = NTAB + REG_A + REG_B;
+  static constexpr int FV_D = REG_A + REG_B;
   static constexpr bool built = LimiterPDE<PDE>::value && N <= (DIM == 2 ? 7 : 3);
   // waves per SIMD of the register budget, blocks of the FV kernel per
   // compute unit, and its persistent grid
@@ -800,7 +799,7 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
               double* __restrict__ sub_out, const uint8_t* __restrict__ status, const LimWork w) {
   using GL = GeoLim<PDE, N>;
   using LC = LimConst<GL::n>;
-  constexpr int DIM = GL::DIM, NV = GL::NV, S = GL::S, NS = GL::NS, NSF = GL::NSF, F = GL::F, NOFF = GL::NOFF;
+  constexpr int DIM = GL::DIM, NV = GL::NV, S = GL::S, NS = GL::NS, F = GL::F, NOFF = GL::NOFF;
   constexpr int m = GL::m, n = GL::n, EB = GL::EB, NB = GL::NB, EC = GL::EC, NC = GL::NC, BLOCK = GL::BLOCK;
   constexpr int NL = ipow(n, DIM - 1), NOY = ipow(3, DIM - 1);
   __shared__ double lds[GL::FV_D];
@@ -811,14 +810,12 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
   // after the step
   __shared__ long long owner2[2][NOFF];
   __shared__ uint8_t fvdata2[2][NOFF], dgface2[2][2 * DIM];
-  double* const T = lds;
-  double* const ra = T + GL::NTAB;
+  double* const ra = lds;
   double* const rb = ra + GL::REG_A;
   double* const box = ra;
   double* const corr = rb;
   double* const ff = rb + NV * NC;  // subface fluxes [d][t][i][v], i = 0..m along d
   const int tid = threadIdx.x;
-  for (int i = tid; i < GL::NTAB; i += BLOCK) T[i] = w.tab[i];
   const double dt = clock[1];
   double ihs[3] = {1.0, 1.0, 1.0};  // 1 / subcell size
 #pragma unroll
