@@ -291,6 +291,9 @@ struct GeoAdjL {
   static constexpr int HAT_ELEMS = HAT + 2 * G::DIM * G::F * G::NP;
   static constexpr int CELL_ELEMS = cmax(cmax(cmax(ROW_ELEMS, HAT_ELEMS), G::NV * G::S),
                                          G::S * (G::NP > 0 ? G::NP : 1));
+  // the corrector's bricks, except for cells of 7^3 nodes (advection, 24^3
+  // cells: a step 293 us in bricks, 285 in order)
+  static constexpr bool BRICKS = G::S < 343;
   static constexpr int by_threads = G::S >= 256 ? 1 : 256 / G::S;
   static constexpr int by_lds = cmax(1, (76 * 1024) / (CELL_ELEMS * 8));
   static constexpr int CPB = cmin(by_threads, by_lds);
@@ -331,7 +334,8 @@ adj_predict_lin_kernel(const KArgs a, const double* __restrict__ Q, const double
     ln[d] = G::line_of(d, kk3[0], kk3[1], DIM == 3 ? kk3[2] : 0);
     pk[d] = LinLayout<G>::addr(d, ln[d], kk3[d]);
   }
-  const long long cell0 = corr_cell0<DIM, CPB>(a, xcd_block(blockIdx.x, a.nblocks));
+  const int lb = xcd_block(blockIdx.x, a.nblocks);
+  const long long cell0 = GA::BRICKS ? corr_cell0<DIM, CPB>(a, lb) : lb * (long long)CPB;
   const long long cell = cell0 + lc;
   const bool active = cell < a.ncells;
   const long long cl = active ? cell : a.ncells - 1;  // clamp loads of the ragged tail
