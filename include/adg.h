@@ -173,8 +173,8 @@ typedef struct {
   long long ncells;      /* C */
   long long state_elems; /* C * nvar * S */
   size_t workspace_bytes; /* device bytes the context holds: face traces
-                            (each trace array also holding C * nparam
-                            doubles for the adjoint where it is built; the
+                            (each trace array also holding C * nparam spare
+                            doubles where the adjoint is built; the
                             second array once adg_run_reserve has run),
                             reduction slots, and the limiter workspace once
                             adg_limiter_reserve has run */

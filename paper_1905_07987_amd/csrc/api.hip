@@ -25,7 +25,9 @@ struct adg_ctx {
   double* traces = nullptr;  // [C][2 dim][2][nv][F]
   double* traces2 = nullptr; // the second trace array of fused runs (adg_run_reserve)
   size_t trace_elems = 0;
-  size_t trace_alloc = 0;    // doubles per trace array: C x np more where the adjoint is built (part of workspace_bytes)
+  // doubles per trace array: C x np more where the adjoint is built.  No kernel
+  // uses those any more; adg_info::workspace_bytes promises them.
+  size_t trace_alloc = 0;
   void* red = nullptr;       // reduction slots
   size_t red_bytes = 0;
   SourceDev* d_src = nullptr;

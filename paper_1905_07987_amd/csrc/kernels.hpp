@@ -143,12 +143,15 @@ struct GeoA1 {
   // y and z continue on the next banks)
   static constexpr int ROW_X = G::S, ROW_Y = G::n == 5 ? 153 : 228, ROW_Z = G::n == 5 ? 153 : G::S;
   static_assert(!NODE_ROWS || C::NFLUX * (ROW_X + ROW_Y + ROW_Z) <= C::NCH * G::SP, "rows exceed the cell's LDS");
-  // Elsewhere the rows' accesses are single ones (the kernel's ALONE) where
-  // that is faster: on 2-D meshes that fill the chip (a step, paired against
-  // single: N = 4, 31000 cells 112.0 and 109.2 us, N = 6 353.8 and 333.2, N =
-  // 3, 612^2 cells 509 and 470); on small ones a wave's chain of single
-  // accesses is longer (N = 3, 4000 cells 18.6 and 33.7 us, N = 6, 4000 cells
-  // 72.0 and 81.8).
+  // Elsewhere the rows' accesses are single ones (the kernel's ALONE) on 2-D
+  // meshes large enough to gain; on small ones a wave's chain of single
+  // accesses is longer.  A step, paired against single: N = 2, 31000 cells
+  // 37.6 and 35.8 us; N = 3, 62500 cells 87.8 and 89.9 (4096: 16.6 and 30.0),
+  // 200000 270.6 and 251.6; 16000 cells at N = 4 66.5 and 63.5, N = 5 102.9 and
+  // 95.2, N = 6 196.9 and 191.2, N = 7 277.8 and 260.3; 4096 cells at N = 4
+  // 26.8 and 28.8, N = 6 70.5 and 79.3.  (The lines lie where every order
+  // gains; the crossings are lower: N = 2 none, N = 3 near 90000 cells, N = 4
+  // 6000, N = 5 4000, N = 6 12000, N = 7 none.)
   static constexpr long long kAloneCells =
       G::DIM != 2 || MF || G::n < 3 ? -1 : (G::n == 3 ? 31000 : (G::n == 4 ? 200000 : 16000));
   __host__ __device__ static constexpr bool alone(long long ncells) { return kAloneCells >= 0 && ncells >= kAloneCells; }
@@ -1375,8 +1378,9 @@ struct FluxCopies<P, kern_void_t<decltype(P::kFluxCopies)>> {
 // sets).  At n = 4 a cell is one wave with node x + 4 y + 16 z on its lane,
 // and v_mfma_f64_4x4x4 contracts along z in place: 8 writes and 36 reads.
 // Measured, one predictor: N = 2, 45 x 38 x 29 cells 147 -> 91 us (4.3 TB/s);
-// N = 3 with the step's keep buffer, 32^3 cells 171 -> 140 us (6.2 TB/s,
-// mostly writes); the adjoint predictor 317 -> 228 us.  Orders 1 to 3: at N = 4 the
+// N = 3 with the step's keep buffer, 32^3 cells 171 -> 140 us (713 MB written
+// and 151 MB read, 6.2 TB/s; a fill reaches 6.2 TB/s on this card, a copy
+// 4.9); the adjoint predictor 317 -> 228 us.  Orders 1 to 3: at N = 4 the
 // gather takes 5 multiplications per derivative against 2.6 of the even-odd
 // line tasks, and 168 registers leave 3 waves per SIMD (a step of 48^3
 // cells 1.48 -> 2.5 ms).

@@ -926,8 +926,6 @@ lim_fv_kernel(const KArgs a, const double* __restrict__ clock, const double* __r
       for (int i = 0; i < EB; ++i) ra[t * EB + i] = out[i];
     }
     __syncthreads();
-    // value of box position (k: offset index of its owner) of the projection,
-    // unless the owner's FV data is taken
     if constexpr (DIM == 3) {
       // along y: one task per (quantity, z offset, kz, x)
       for (int t = tid; t < NV * 3 * n * EB; t += BLOCK) {

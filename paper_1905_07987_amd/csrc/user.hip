@@ -162,11 +162,11 @@ adg_status user_module_create(const char* source, const std::string& arch, int o
   const std::string src = prelude(source) + "extern \"C\" __constant__ int adg_user_geo[4] = {" + geo +
                           "::BLOCK, " + geo + "::CPB, " + gb + "::BLOCK, " + gb + "::CPB};\n";
   std::vector<std::string> names = {"&" + pred,
-                                          "&adg::correct_kernel<" + UP + ", " + N + ">",
-                                          "&adg::lambda_kernel<" + UP + ", " + N + ">",
-                                          "&adg::admissible_kernel<" + UP + ", " + N + ">",
-                                          "&adg::finalize_kernel",
-                                          "&adg::count_kernel"};
+                                    "&adg::correct_kernel<" + UP + ", " + N + ">",
+                                    "&adg::lambda_kernel<" + UP + ", " + N + ">",
+                                    "&adg::admissible_kernel<" + UP + ", " + N + ">",
+                                    "&adg::finalize_kernel",
+                                    "&adg::count_kernel"};
   if (!pred_src.empty()) names.push_back("&" + pred_src);
   Compiled c;
   adg_status st = rtc_compile(src, names, arch, &c, err);

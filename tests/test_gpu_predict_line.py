@@ -165,3 +165,28 @@ def test_two_dimensional_rules_against_oracle(order, cells, iters):
     torch.cuda.synchronize()
     assert rel_l2(Q.cpu().numpy(), Qo) <= TOL
     s.close()
+
+
+@pytest.mark.parametrize("order,tiles", [(2, [12, 12]), (3, [31, 30]), (4, [9, 9]), (5, [9, 9]), (6, [9, 9]), (7, [9, 9])])
+def test_fp32_single_accesses_are_the_paired_ones_bitwise(order, tiles):
+    """2-D meshes on which the FP32 predictor accesses its rows one element at
+    a time: a periodic mesh of 13 x 17 cells, repeated until it has as many
+    cells, steps bitwise as the small one, whose rows are accessed in pairs
+    (itself against the oracle, 1e-5).  The last block is part full."""
+    print("[gpu-test] fp32 single accesses", order, tiles, flush=True)
+    small, h = [13, 17], 1.0 / 16
+    P = O.problem(2, order, O.EULER, small, [0.0, 0.0], [n * h for n in small], cfl=0.4)
+    x = O.node_coords(P) * (1.0 / np.array([n * h for n in small]))
+    Q0 = inputs.smooth_euler_state(x, 37)
+    dt = O.stable_dt(P, Q0)[0]
+    out = []
+    for t in ([1, 1], tiles):
+        cells = [n * k for n, k in zip(small, t)]
+        s = adg.Solver(2, order, "euler", cells, [0.0, 0.0], [n * h for n in cells], cfl=0.4, precision="fp32")
+        Q = dev(np.tile(Q0.reshape(small[1], small[0], 4, -1), (t[1], t[0], 1, 1)).reshape(s.state_shape))
+        s.step(Q, None, dev([0.0, dt]), next_dt=False)
+        torch.cuda.synchronize()
+        out.append(Q.view(t[1], small[1], t[0], small[0], 4, -1))
+        s.close()
+    assert rel_l2(out[0].cpu().numpy().reshape(Q0.shape), O.step(P, Q0, None, dt, 0.0)) <= 1e-5
+    assert torch.equal(out[1], out[0].expand_as(out[1]))
