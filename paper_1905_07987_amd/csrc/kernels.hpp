@@ -135,9 +135,16 @@ struct GeoA1 {
   // 5, 40^3 cells 3.45 -> 3.00 ms.
   // (Every line of a direction is one task, all in one round: run-time PDEs of
   // more quantities than that leaves threads for, 6 or more at n = 5 and 7 or
-  // more at n = 6, keep the other rows.)
-  static constexpr bool NODE_ROWS = !MF && G::DIM == 3 && (G::n == 5 || G::n == 6) && sizeof(R) == 4 &&
-                                    C::ngrad() == 0 && CPB * C::NFLUX * G::F <= BLOCK;
+  // more at n = 6, keep the other rows.  So do, at n = 6, those of fewer than
+  // five, whose tasks leave most threads idle, and of six with a source term
+  // (a step of 6^3 and 18^3 cells, other rows against these: 1 quantity 15.2
+  // and 21.0 us, 78.0 and 85.0; 3 26.0 and 28.1, 192 and 169; 4 27.9 and 31.0,
+  // 248 and 230; 5 38.1 and 36.8, 373 and 310; 6 41.1 and 40.1, 420 and 382,
+  // with a source term 46.4 and 49.5, 478 and 488).  At n = 5 all of up to
+  // five gain: 1 quantity 19.4 and 18.2, 50.1 and 43.2.)
+  static constexpr bool NODE_ROWS =
+      !MF && G::DIM == 3 && sizeof(R) == 4 && C::ngrad() == 0 && CPB * C::NFLUX * G::F <= BLOCK &&
+      (G::n == 5 || (G::n == 6 && (C::NFLUX == 5 || (C::NFLUX == 6 && !PDE::kHasSource))));
   static constexpr int YS = G::n == 5 ? 27 : 38;               // between the points of a y-line
   // elements of a row of each direction (n = 5: the next channel's lines of
   // y and z continue on the next banks)
