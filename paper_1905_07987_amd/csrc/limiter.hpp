@@ -784,7 +784,7 @@ __device__ __forceinline__ void lim_extend(const double (&own)[n], const double 
 
 // FV cells, a persistent grid over the FV list.  Bound by the latency of its
 // phases, each about one round of dependent FP64 work and LDS accesses, with
-// one block of twelve waves per compute unit (3-D N = 3: 141 KB of LDS; per
+// one block of twelve waves per compute unit (3-D N = 3: 138 KiB of LDS; per
 // cell 54,000 cycles, the slopes and half-step corrections 12,000, the owners'
 // data 10,000, the subface fluxes 8,700).  The box of subcell averages is a
 // tensor-product projection, an axis at a time over the cell and its
