@@ -223,11 +223,13 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
     }
   };
   bool src_here = false;
-  unsigned src_mine = 0;  // the sources in this thread's cell (looked up once: each look is a wait for memory)
+  // The sources in this thread's cell (looked up once: each look is a wait for
+  // memory); the same for the block where it holds one cell.
+  unsigned src_mine = 0;
   for (int s = 0; s < a.nsrc; ++s) {
     const long long c = a.src[s].cell;
     src_here = src_here || (c >= cell0 && c < cell0 + CPB);
-    src_mine |= c == cell && node ? 1u << s : 0u;
+    src_mine |= c == (CPB == 1 ? cell0 : cell) ? 1u << s : 0u;
   }
   if (src_here) {
     // (a block of one wave has fewer threads than 16 sources have entries)
@@ -240,7 +242,8 @@ predict_kernel_n64(const KArgs a, const double* Q, const double* __restrict__ pa
   }
   // (made visible by the first barrier below)
   auto add_point_sources = [&](int j, double* Sv, double sgn = 1.0) {
-    if (!src_here) return;
+    if (CPB == 1 ? src_mine == 0 : !src_here) return;
+    if (!node) return;
     for (unsigned m = src_mine; m; m &= m - 1) {
       const int s = __builtin_ctz(m);
       const double amp = src_amp(s * NA + j);
